@@ -163,10 +163,18 @@ __device__ __forceinline__ float block_sum(float v, float* scratch) {
 // ---------------------------------------------------------------------------
 __device__ __forceinline__ float swish_f(float z) { return z / (1.0f + __expf(-z)); }
 
+// GELU, tanh form: z/2 (1 + tanh u) = z / (1 + e^{-2u}), u = sqrt(2/pi)
+// (z + 0.044715 z^3).  One exponential, one reciprocal and five multiply-adds
+// where the library's tanhf takes several tens of instructions, which the
+// many-row epilogues are bound by (batch-64 pi0 41.9 -> 40.4 ms, 96-image
+// tower 6.41 -> 6.21 ms over six blocks).  Error against 64 bits 1.1-1.8e-7 of the
+// value for z > -0.1; for z < 0 it also avoids the cancellation in 1 + tanh u
+// (8e-4 -> 9e-7 of the value on -4 .. -2).
 __device__ __forceinline__ float gelu_tanh_f(float z) {
-  const float k0 = 0.7978845608028654f;   // sqrt(2/pi)
-  const float u = k0 * (z + 0.044715f * z * z * z);
-  return 0.5f * z * (1.0f + tanhf(u));
+  constexpr float c1 = -2.302208198144325f;   // -2 log2(e) sqrt(2/pi)
+  constexpr float c3 = -0.1029432395800235f;  // c1 * 0.044715
+  const float e = __builtin_amdgcn_exp2f(z * fmaf(c3, z * z, c1));
+  return z * __builtin_amdgcn_rcpf(1.0f + e);
 }
 
 enum Act { ACT_NONE = 0, ACT_SWISH = 1, ACT_GELU = 2 };
