@@ -15,7 +15,8 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 OUT = os.path.join(HERE, "libphyai.so")
-SOURCES = ["gemm.hip", "attention.hip", "rowops.hip", "runtime.hip", "persist.hip"]
+SOURCES = ["gemm.hip", "gemm_wide_store.hip", "gemm_wide_resid.hip", "gemm_wide_geglu.hip", "gemm_wide_qkv.hip",
+           "gemm_wide_kv.hip", "attention.hip", "rowops.hip", "runtime.hip", "persist.hip"]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-Wall", "-Wno-unused-function",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",

@@ -7,7 +7,7 @@
 //   fp8 : 16 bytes per lane, same k order, one byte per value
 // for packed column 32p + 16hf + l%16.  A wave streaming one pair tile along
 // K therefore reads whole contiguous 2 KiB (bf16) / 1 KiB (fp8) blocks.
-#include "kernels.hpp"
+#include "gemm_tile.hpp"
 
 #include <cstdlib>
 #include <cstring>
@@ -18,20 +18,6 @@ namespace phyai {
 namespace {
 
 constexpr int kMT = 4;           // 16-row MFMA tiles per block (64 rows)
-
-typedef unsigned int u32x4_t __attribute__((ext_vector_type(4)));
-typedef const __attribute__((address_space(1))) u32x4_t gu32x4_t;
-
-// 16-, 8- and 2-byte loads through a global (not generic) pointer, which the
-// compiler counts with vmcnt alone
-__device__ __forceinline__ u32x4_t gload16(const void* p) { return *(gu32x4_t*)(p); }
-typedef unsigned int u32x2_t __attribute__((ext_vector_type(2)));
-__device__ __forceinline__ u32x2_t gload8(const void* p) {
-  return *(const __attribute__((address_space(1))) u32x2_t*)(p);
-}
-__device__ __forceinline__ uint32_t gload2(const void* p) {
-  return *(const __attribute__((address_space(1))) uint16_t*)(p);
-}
 
 // The two 8-value k-steps of lane `lane`'s weight fragment (pair tile p,
 // k-block kb, half hf) as bf16 MFMA operands, for the stored weight kinds:
@@ -400,40 +386,17 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(GemmArgs g, Epi epi) {
   epi(row, p, c, t0, t1);
 }
 
-// ---------------------------------------------------------------------------
-// Tiled GEMM for many rows (rollout batches): 128 x 128 output tiles, 4 waves
-// in a 2 x 2 arrangement of 64 x 64.  Per k-block of 64 the activation tile
-// (128 x 64 bf16, 16-byte chunks XOR-swizzled against bank conflicts) and
-// the block's 8 packed weight fragments are copied into LDS by direct
-// global->LDS loads, double-buffered; fp8 codes are expanded to bf16 after
-// the LDS read.  A grid-stride loop walks the output tiles.
-// ---------------------------------------------------------------------------
-typedef __attribute__((address_space(3))) void lds_void_t;
-
-__device__ __forceinline__ void dma16(const void* src, lds_void_t* lds) {
-  const uint32_t m = static_cast<uint32_t>(reinterpret_cast<uintptr_t>(lds));
-  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" :: "s"(m), "v"(src) : "memory", "m0");
-}
-#define GEMM_WAIT_VMCNT(n) __builtin_amdgcn_s_waitcnt(((n) & 15) | (((n) >> 4) << 14) | 0x70 | 0xF00)
-__device__ __forceinline__ void bare_barrier() {
-  __builtin_amdgcn_s_waitcnt(0xC07F);   // lgkmcnt(0)
-  __builtin_amdgcn_s_barrier();
-}
-__device__ __forceinline__ int aswz(int row) { return (row >> 1) & 7; }
-
 // XCD-aware tile order of the many-row GEMMs.  Blocks are dealt to the 8 XCDs
 // round-robin and each XCD has its own L2, so with a plain order every XCD
 // streams all of A and all of W.  When W is the larger operand the 128 x 128
 // tiles are put in bands of kBand column tiles, row by row within a band,
 // and XCD x takes the x-th eighth of that order (block b runs position
-// (b % 8) * per + b / 8, plus multiples of the grid's share per XCD): an XCD
-// then streams about one band of W.  Otherwise (and for the QKV epilogue,
+// (b % 8) * per + b / 8): an XCD then streams about one band of W.  Otherwise (and for the QKV epilogue,
 // whose cost differs a lot between bands because of the transposed V
 // stores) the plain order is kept: row tile fastest over the block index.
 // With one tile per CU (the four-stage ring) and the activations the larger
 // operand, the tiles go row by row and XCD x takes the x-th eighth, so that
-// each activation row tile is streamed by one XCD.  (For the grid-strided
-// kernel that row split measured no better than the plain order.)
+// each activation row tile is streamed by one XCD.
 constexpr int kOrderPlain = 0, kOrderRows = 1, kOrderBands = 2;
 constexpr int kBand = 8;
 __host__ __device__ inline int gemm_tiles(const GemmArgs& g) { return ((g.R + 127) / 128) * (g.NPT / 4); }
@@ -468,87 +431,36 @@ __device__ __forceinline__ void tile_at(int t, int mtiles, int ntiles, int order
     ni = band * kBand + rem % bw;
   }
 }
-// The j-th tile of block b (j = 0, 1, ...) under the XCD split, -1 past the end;
-// the grid is a multiple of 8.
-__device__ __forceinline__ int xcd_tile(int b, int j, int grid, int T, int order) {
-  if (order == kOrderPlain) {
-    const int t = b + j * grid;
-    return t < T ? t : -1;
-  }
+// The tile of block b under the XCD split, -1 past the end; the grid is a
+// multiple of 8.
+__device__ __forceinline__ int xcd_tile(int b, int T, int order) {
+  if (order == kOrderPlain) return b < T ? b : -1;
   const int per = (T + 7) / 8;
-  const int k = b / 8 + j * (grid / 8);
-  const int t = (b % 8) * per + k;
+  const int k = b / 8, t = (b % 8) * per + k;
   return (k < per && t < T) ? t : -1;
 }
-// Grid for T tiles with at most `cap` blocks: a multiple of 8.
-inline int xcd_grid(int T, int cap) {
-  const int g = 8 * ((T + 7) / 8);
-  return g < cap ? g : cap;
-}
+// Grid for T tiles, one block each: a multiple of 8.
+inline int xcd_grid(int T) { return 8 * ((T + 7) / 8); }
 
 
-// Epilogue of a wave's 64 x 64 tile (4 x 4 MFMA tiles, two pair tiles):
-// every load the epilogue needs (residual rows, biases, RoPE factors) is
-// requested for all 32 elements of the lane before the first store, so the
-// tile costs one memory round trip instead of one per element.
-// Epilogue of a 64x32 wave tile held as acc[mt][n16][v] (rows r0 + 16mt + 4lg
-// + v, pair tiles p0 and p0 + 1).  The element loads of MG row groups are
-// requested together before any of their stores; MG trades registers (and so
-// occupancy) against memory round trips.  MG = 0 finishes each element before
-// loading the next.
-template <int MG, class Epi, int NT>
+// Epilogue of a wave tile held as acc[mt][n16][v] (rows r0 + 16mt + 4lg + v,
+// pair tiles p0 ..), each element finished before the next one's loads:
+// requesting them together cost the two-stage ring a wave per SIMD.
+template <class Epi, int NT>
 __device__ __forceinline__ void tile_epilogue(const GemmArgs& g, const Epi& epi, const f32x4 (&acc)[4][NT], int r0,
                                               int p0, int lc, int lg) {
-  static_assert(MG == 0 || 4 % MG == 0, "row groups come in 4s");
-  constexpr int NP = NT / 2;                  // pair tiles of the wave tile
-  if constexpr (MG == 0) {
 #pragma unroll
-    for (int pp = 0; pp < NP; ++pp) {
-      const int p = p0 + pp;
-      const float s0c = g.scale ? g.scale[32 * p + lc] : 1.f;
-      const float s1c = g.scale ? g.scale[32 * p + 16 + lc] : 1.f;
+  for (int pp = 0; pp < NT / 2; ++pp) {
+    const int p = p0 + pp;
+    const float s0c = g.scale ? g.scale[32 * p + lc] : 1.f;
+    const float s1c = g.scale ? g.scale[32 * p + 16 + lc] : 1.f;
 #pragma unroll
-      for (int mt = 0; mt < 4; ++mt)
+    for (int mt = 0; mt < 4; ++mt)
 #pragma unroll
-        for (int v = 0; v < 4; ++v) {
-          const int row = r0 + 16 * mt + 4 * lg + v;
-          if (row < g.R) epi(row, p, lc, acc[mt][2 * pp][v] * s0c, acc[mt][2 * pp + 1][v] * s1c);
-        }
-    }
-    return;
-  }
-  typename Epi::ColPre cpre[NP];
-  float sc[NP][2];
-#pragma unroll
-  for (int pp = 0; pp < NP; ++pp) {
-    cpre[pp] = epi.colpre(p0 + pp, lc);
-    sc[pp][0] = g.scale ? g.scale[32 * (p0 + pp) + lc] : 1.f;
-    sc[pp][1] = g.scale ? g.scale[32 * (p0 + pp) + 16 + lc] : 1.f;
-  }
-  constexpr int MS = MG > 0 ? MG : 4;
-#pragma unroll
-  for (int m0 = 0; m0 < 4; m0 += MS) {
-    typename Epi::Pre pre[NP][MS][4];
-#pragma unroll
-    for (int pp = 0; pp < NP; ++pp)
-#pragma unroll
-      for (int mi = 0; mi < MS; ++mi)
-#pragma unroll
-        for (int v = 0; v < 4; ++v) {
-          const int row = r0 + 16 * (m0 + mi) + 4 * lg + v;
-          if (row < g.R) pre[pp][mi][v] = epi.pre(row, p0 + pp, lc);
-        }
-#pragma unroll
-    for (int pp = 0; pp < NP; ++pp)
-#pragma unroll
-      for (int mi = 0; mi < MS; ++mi)
-#pragma unroll
-        for (int v = 0; v < 4; ++v) {
-          const int row = r0 + 16 * (m0 + mi) + 4 * lg + v;
-          if (row < g.R)
-            epi.apply(row, p0 + pp, lc, cpre[pp], pre[pp][mi][v], acc[m0 + mi][2 * pp][v] * sc[pp][0],
-                      acc[m0 + mi][2 * pp + 1][v] * sc[pp][1]);
-        }
+      for (int v = 0; v < 4; ++v) {
+        const int row = r0 + 16 * mt + 4 * lg + v;
+        if (row < g.R) epi(row, p, lc, acc[mt][2 * pp][v] * s0c, acc[mt][2 * pp + 1][v] * s1c);
+      }
   }
 }
 
@@ -575,128 +487,15 @@ __device__ __forceinline__ void tile_epilogue_early(const GemmArgs& g, const Epi
   }
 }
 
-template <bool FP8>
-struct TiledSmem {
-  bf16_t A[128 * 64];
-  uint8_t B[8 * (FP8 ? 1024 : 2048)];
-};
-
-template <class Epi, bool FP8>
-__global__ __launch_bounds__(256, 2) void gemm_tiled_kernel(GemmArgs g, Epi epi) {
-  __shared__ __attribute__((aligned(1024))) TiledSmem<FP8> s0;
-  __shared__ __attribute__((aligned(1024))) TiledSmem<FP8> s1;
-  constexpr int FB = FP8 ? 1024 : 2048;          // bytes per weight fragment
-  constexpr int NB = 8 * FB / 1024 / 4;          // weight DMA blocks per wave per k-block
-  constexpr int NOPS = 4 + NB;                   // DMA ops per thread per k-block
-  const int wave = threadIdx.x / kWave, lane = threadIdx.x % kWave;
-  const int wv = __builtin_amdgcn_readfirstlane(wave);
-  const int wm = wave >> 1, wn = wave & 1;
-  const int lc = lane % 16, lg = lane / 16;
-  const int nkb = g.K / 64;
-  const int mtiles = (g.R + 127) / 128, ntiles = g.NPT / 4;
-  const bf16_t* A = static_cast<const bf16_t*>(g.A);
-  const uint8_t* W = static_cast<const uint8_t*>(g.W);
-
-  // per-thread A source offsets (row within tile, swizzled chunk) for loads i = 0..3
-  int arow[4], acol[4];
-#pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    const int pos = (4 * i + wave) * 64 + lane;
-    arow[i] = pos / 8;
-    acol[i] = 8 * ((pos % 8) ^ aswz(pos / 8));
-  }
-
-  const int order = tile_order(g, Epi::kWaveTile);
-  for (int j = 0;; ++j) {
-    const int tile = xcd_tile(blockIdx.x, j, gridDim.x, mtiles * ntiles, order);
-    if (tile < 0) break;
-    int mi, ni;
-    tile_at(tile, mtiles, ntiles, order, g.R % 128 != 0, mi, ni);
-    const int mt0 = mi * 128;
-    const int pt0 = ni * 4;
-    int aoff[4];       // element offsets of this thread's A chunks (rows clamped into range)
-#pragma unroll
-    for (int i = 0; i < 4; ++i) aoff[i] = min(mt0 + arow[i], g.R - 1) * g.lda + acol[i];
-
-    auto issue = [&](TiledSmem<FP8>& S, int kb) {
-#pragma unroll
-      for (int i = 0; i < 4; ++i) dma16(A + aoff[i] + kb * 64, (lds_void_t*)(S.A + (4 * i + wv) * 512));
-#pragma unroll
-      for (int i = 0; i < NB; ++i) {
-        const int blk = 4 * i + wv;                  // 1 KiB block of the k-block's weights
-        const int f = blk / (FB / 1024), part = blk % (FB / 1024);
-        const int p = pt0 + f / 2, hf = f % 2;
-        const uint8_t* src = W + ((int64_t)(p * nkb + kb) * 2 + hf) * FB + part * 1024 + lane * 16;
-        dma16(src, (lds_void_t*)(S.B + blk * 1024));
-      }
-    };
-
-    f32x4 acc[4][4];
-#pragma unroll
-    for (int i = 0; i < 4; ++i)
-#pragma unroll
-      for (int j = 0; j < 4; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
-
-    auto compute = [&](const TiledSmem<FP8>& S) {
-      bf16x8 af[4][2];
-#pragma unroll
-      for (int mt = 0; mt < 4; ++mt) {
-        const int row = 64 * wm + 16 * mt + lc;
-#pragma unroll
-        for (int st = 0; st < 2; ++st)
-          af[mt][st] = *reinterpret_cast<const bf16x8*>(S.A + row * 64 + 8 * ((4 * st + lg) ^ aswz(row)));
-      }
-      bf16x8 bfr[4][2];
-#pragma unroll
-      for (int nt = 0; nt < 4; ++nt) {
-        const int f = (2 * wn + nt / 2) * 2 + nt % 2;
-        if (FP8) {
-          const uint4 v = *reinterpret_cast<const uint4*>(S.B + f * FB + lane * 16);
-          bfr[nt][0] = fp8x8_to_bf16x8(v.x, v.y);
-          bfr[nt][1] = fp8x8_to_bf16x8(v.z, v.w);
-        } else {
-          const uint4* src = reinterpret_cast<const uint4*>(S.B + f * FB + lane * 32);
-          bfr[nt][0] = as_bf16x8(src[0]);
-          bfr[nt][1] = as_bf16x8(src[1]);
-        }
-      }
-#pragma unroll
-      for (int st = 0; st < 2; ++st)
-#pragma unroll
-        for (int mt = 0; mt < 4; ++mt)
-#pragma unroll
-          for (int nt = 0; nt < 4; ++nt) acc[mt][nt] = mfma16x16x32(af[mt][st], bfr[nt][st], acc[mt][nt]);
-    };
-
-    issue(s0, 0);
-    for (int kb = 0; kb < nkb; kb += 2) {
-      if (kb + 1 < nkb) { issue(s1, kb + 1); GEMM_WAIT_VMCNT(NOPS); } else { GEMM_WAIT_VMCNT(0); }
-      bare_barrier();
-      compute(s0);
-      bare_barrier();
-      if (kb + 1 >= nkb) break;
-      if (kb + 2 < nkb) { issue(s0, kb + 2); GEMM_WAIT_VMCNT(NOPS); } else { GEMM_WAIT_VMCNT(0); }
-      bare_barrier();
-      compute(s1);
-      bare_barrier();
-    }
-
-    // epilogue: wave (wm, wn) holds rows mt0+64wm.., pair tiles pt0+2wn, +1
-    if constexpr (Epi::kWaveTile) epi.wave_tile(g, acc, mt0 + 64 * wm, pt0 + 2 * wn, lc, lg);
-    else tile_epilogue<4>(g, epi, acc, mt0 + 64 * wm, pt0 + 2 * wn, lc, lg);
-  }
-}
-
 // ---------------------------------------------------------------------------
 // Ring-pipelined 128 x 128 GEMM for many rows.  Waves in a 2 x 2 (64 x 64
 // wave tiles) or 2 x 4 (64 x 32) arrangement; per k-block of 64 the
 // activation tile and the block's 8 packed weight fragments go through an
 // LDS ring of 2 or 4 stages (48 / 96 KiB per block for fp8 weights); one
 // barrier per k-block; every fragment of a k-block is requested before its
-// first MFMA.  On the rollout-batch shapes (3264 rows, fp8 weights) the
-// two-stage form beat the grid-strided kernel above for K = 1024 (QKV 28.5
-// vs 39 us, GeGLU 65 vs 77 us), and the four-stage eight-wave form beats
-// both wherever a GEMM has at most one tile per CU (O 23.5, down 38.7 us).
+// first MFMA.  Used for widths that are no multiple of 256 columns and, in
+// the four-stage eight-wave form (at most one tile per CU), for K splits,
+// where it beats the 256-column kernel of gemm_wide.hpp.
 // ---------------------------------------------------------------------------
 template <bool FP8, int NW = 4>
 struct RingCfg {
@@ -729,7 +528,7 @@ gemm_ring_kernel(GemmArgs g, Epi epi) {
   const int lc = lane % 16, lg = lane / 16;
   const int mtiles = (g.R + 127) / 128, ntiles = g.NPT / 4;
   const int order = tile_order(g, Epi::kWaveTile, NS == 4);
-  const int t = xcd_tile(blockIdx.x, 0, gridDim.x, mtiles * ntiles, order);
+  const int t = xcd_tile(blockIdx.x, mtiles * ntiles, order);
   if (t < 0) return;
   int mi, ni;
   tile_at(t, mtiles, ntiles, order, g.R % 128 != 0, mi, ni);
@@ -879,7 +678,7 @@ gemm_ring_kernel(GemmArgs g, Epi epi) {
       tile_epilogue_early<Epi, NT>(g, epi, acc, m0 + 64 * wm, pt0 + (NT / 2) * wn, lc, lg, epre, esc);
     }
   } else {
-    tile_epilogue<0>(g, epi, acc, m0 + 64 * wm, pt0 + (NT / 2) * wn, lc, lg);
+    tile_epilogue(g, epi, acc, m0 + 64 * wm, pt0 + (NT / 2) * wn, lc, lg);
   }
 }
 
@@ -1078,38 +877,84 @@ int small_row_tiles(int R, int NPT) {
   return kMT;
 }
 
+// The tile of the 256-column kernel for a GEMM of at least 256 rows (mt = 0:
+// not taken).  Where tiles of up to 64 rows need at most one block per CU, the
+// smallest such with four stages: fewer rows per block finish sooner (768 x
+// 1024 x 3072: 48 rows 13.3 us, 64 rows 15.1, 128 x 128 ring 18).  Otherwise
+// two stages and the tile that finishes first by the measured cost of a tile's
+// k-block, about 3 + mt (144 rows: 13; a second operand term doubles the mt
+// part), times the tiles of the fullest CU; a lone tile also pays for its own
+// start and epilogue, which no neighbour covers (56, some 5 us).
+// PHYAI_WIDE_TILE=<mt>x<ns> (tests, read at enqueue time) forces one.
+WideTile wide_tile(const GemmArgs& g) {
+  const WideTile none{0, 0};
+  if (g.R < 256 || g.NPT % 8 != 0 || (g.kind != W_BF16 && g.kind != W_FP8)) return none;
+  if (getenv("PHYAI_GEMM_TILE")) return none;       // tests: a 128 x 128 kernel is forced
+  const int nz = g.split_out ? g.split_k : 1;
+  const bool deep = g.K / 64 / nz >= 3;             // what four stages need
+  if (const char* f = getenv("PHYAI_WIDE_TILE")) {
+    const bool four = strstr(f, "x4") != nullptr;
+    return four && !deep ? WideTile{4, 2} : WideTile{atoi(f), four ? 4 : 2};
+  }
+  auto tiles = [&](int mt) { return (int64_t)((g.R + 16 * mt - 1) / (16 * mt)) * (g.NPT / 8) * nz; };
+  if (deep)
+    for (int mt : {2, 3, 4})
+      if (tiles(mt) <= 256) return WideTile{mt, 4};
+  WideTile best = none;
+  int64_t least = 0;
+  for (int mt : {4, 7, 8, 9}) {
+    const int64_t per = (tiles(mt) + 255) / 256;
+    const int64_t cost = per * (3 + (mt == 9 ? 10 : mt) * (g.A_lo ? 2 : 1)) * (g.K / 64 / nz) + (per == 1 ? 56 : 0);
+    if (best.mt == 0 || cost < least) {
+      best = WideTile{mt, 2};
+      least = cost;
+    }
+  }
+  return best;
+}
+
+template <class Epi> struct WideEpi : std::true_type {};
+template <> struct WideEpi<EpiGeglu<float>> : std::false_type {};
+template <> struct WideEpi<EpiQkv<float>> : std::false_type {};
+template <> struct WideEpi<EpiKV<float>> : std::false_type {};
+
 template <class Epi>
 void launch(const GemmArgs& g, const Epi& epi, hipStream_t s) {
+  if constexpr (WideEpi<Epi>::value) {
+    const WideTile t = wide_tile(g);
+    // a K split without a second operand term keeps the 128 x 128 ring: its few
+    // tiles (768 x 4096 x 1024, 816 x 16384 x 2048) pay for the wide blocks' weight
+    // re-reads (tower 1.90 against 1.95 ms, prefix LM 0.87 against 0.95)
+    if (t.mt > 0 && !(g.split_out && !g.A_lo)) {
+      gemm_wide(g, epi, t, s);
+      return;
+    }
+  }
   if (g.kind == W_F32) {
     dim3 grid(g.NPT, (g.R + 15) / 16);
     hipLaunchKernelGGL(gemm_f32_kernel<Epi>, grid, dim3(256), 0, s, g, epi);
   } else if (g.R >= 256 && g.A_lo == nullptr && g.A_ind == nullptr && g.rows_per_req == 0 && g.NPT % 4 == 0 &&
              g.kind != W_FP4) {
     const int tiles = gemm_tiles(g);
-    const char* force = getenv("PHYAI_GEMM_TILE");   // tests: "ring" / "deep" / "strided" (read at enqueue time)
-    // at most one tile per CU: no second block covers the load latency, so
-    // the four-stage ring with eight waves (two per SIMD); otherwise the
-    // two-stage ring for short K and the strided kernel for long K
+    const char* force = getenv("PHYAI_GEMM_TILE");   // tests: "ring" / "deep" (read at enqueue time)
+    // widths that are no multiple of 256, and K splits (see above).  At most one
+    // tile per CU: no second block covers the load latency, so the four-stage
+    // ring with eight waves (two per SIMD); otherwise the two-stage ring
     const int nz = g.split_out ? g.split_k : 1;       // K slices (gemm_split_k), deep ring only
     const bool deep = !Epi::kWaveTile && (nz > 1 || (force ? strcmp(force, "deep") == 0 : tiles <= 256));
-    const bool ring = force ? strcmp(force, "strided") != 0 : g.K <= 2048;
     if (deep) {
-      const dim3 rgrid(xcd_grid(tiles, 1 << 30), nz);
+      const dim3 rgrid(xcd_grid(tiles), nz);
       if constexpr (!Epi::kWaveTile) {
         if (g.kind == W_FP8) hipLaunchKernelGGL((gemm_ring_kernel<Epi, true, 4, 4>), rgrid, dim3(512), 0, s, g, epi);
         else hipLaunchKernelGGL((gemm_ring_kernel<Epi, false, 4, 4>), rgrid, dim3(512), 0, s, g, epi);
       }
-    } else if (ring) {
+    } else {
       // eight waves per block too, except for the QKV epilogue, whose wave-tile
       // form is written for 64 x 64 wave tiles
-      const dim3 rgrid(xcd_grid(tiles, 1 << 30));
+      const dim3 rgrid(xcd_grid(tiles));
       constexpr int WN = Epi::kWaveTile ? 2 : 4;
       if (g.kind == W_FP8) hipLaunchKernelGGL((gemm_ring_kernel<Epi, true, 2, WN>), rgrid, dim3(128 * WN), 0, s, g, epi);
       else hipLaunchKernelGGL((gemm_ring_kernel<Epi, false, 2, WN>), rgrid, dim3(128 * WN), 0, s, g, epi);
-    } else {
-      dim3 grid(xcd_grid(tiles, 512));
-      if (g.kind == W_FP8) hipLaunchKernelGGL((gemm_tiled_kernel<Epi, true>), grid, dim3(256), 0, s, g, epi);
-      else hipLaunchKernelGGL((gemm_tiled_kernel<Epi, false>), grid, dim3(256), 0, s, g, epi);
     }
   } else {
     // 32 columns and 16 * MT rows per block; K split over blockIdx.z only

@@ -1,0 +1,15 @@
+#include "gemm_wide.hpp"
+
+namespace phyai {
+
+void gemm_wide(const GemmArgs& g, const EpiResid& e, WideTile t, hipStream_t s) {
+  if (g.A_lo) {
+    if (g.kind == W_FP8) wide_launch<EpiResid, true, W_FP8>(g, e, t, s);
+    else wide_launch<EpiResid, true, W_BF16>(g, e, t, s);
+    return;
+  }
+  if (g.kind == W_FP8) wide_launch<EpiResid, false, W_FP8>(g, e, t, s);
+  else wide_launch<EpiResid, false, W_BF16>(g, e, t, s);
+}
+
+}  // namespace phyai

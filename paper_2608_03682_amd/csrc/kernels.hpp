@@ -424,6 +424,17 @@ struct EpiKV {
   }
 };
 
+// The 256-column kernel's tile: 16 mt rows, ns stages (mt = 0: not taken).
+struct WideTile {
+  int mt, ns;
+};
+void gemm_wide(const GemmArgs&, const EpiStore<bf16_t>&, WideTile, hipStream_t);
+void gemm_wide(const GemmArgs&, const EpiStore<float>&, WideTile, hipStream_t);
+void gemm_wide(const GemmArgs&, const EpiResid&, WideTile, hipStream_t);
+void gemm_wide(const GemmArgs&, const EpiGeglu<bf16_t>&, WideTile, hipStream_t);
+void gemm_wide(const GemmArgs&, const EpiQkv<bf16_t>&, WideTile, hipStream_t);
+void gemm_wide(const GemmArgs&, const EpiKV<bf16_t>&, WideTile, hipStream_t);
+
 void gemm_store_bf16(const GemmArgs&, const EpiStore<bf16_t>&, hipStream_t);
 void gemm_store_f32(const GemmArgs&, const EpiStore<float>&, hipStream_t);
 void gemm_resid(const GemmArgs&, const EpiResid&, hipStream_t);
