@@ -325,26 +325,30 @@ __global__ __launch_bounds__(256) void gemm_mfma_kernel(GemmArgs g, Epi epi) {
   }
 }
 
-// fp32 path: weights stored [K][N] (packed column order).  Block: 16 rows x
+// fp32 path: weights stored [K][N] (packed column order).  Block: RB rows x
 // one pair tile (32 columns); K is split over 16 slices (thread = slice kq,
-// column c), each slice accumulating all 16 rows of its two columns with
+// column c), each slice accumulating all RB rows of its two columns with
 // 16-byte loads of four consecutive k of a row, and the slices are summed
 // through LDS in slice order.  K a multiple of 64 (every K of the configs).
-template <class Epi>
+// With few rows the chain of loads along a slice bounds it: RB = 4 gives four
+// times the blocks and, with fewer accumulators, loads of several steps in
+// flight (tiny expert: the residual GEMMs, K = 256 and 1024, 11.2 -> 6.8 us).
+template <class Epi, int RB>
 __global__ __launch_bounds__(256) void gemm_f32_kernel(GemmArgs g, Epi epi) {
-  __shared__ float red[16][16][33];             // [slice][row][column], padded
+  __shared__ float red[16][RB][33];             // [slice][row][column], padded
   const int c = threadIdx.x % 16, kq = threadIdx.x / 16;
   const int p = blockIdx.x;
-  const int r0 = blockIdx.y * 16;
+  const int r0 = blockIdx.y * RB;
   const float* A = g.A_ind ? static_cast<const float*>(*g.A_ind) + g.a_off
                            : static_cast<const float*>(g.A);
   const float* w = static_cast<const float*>(g.W) + 32 * p + c;
   const int N = 32 * g.NPT;
   const int kc = g.K / 16;                      // slice length, a multiple of 4
   const int k0 = kq * kc;
-  float s0[16], s1[16];
+  float s0[RB], s1[RB];
 #pragma unroll
-  for (int r = 0; r < 16; ++r) s0[r] = s1[r] = 0.f;
+  for (int r = 0; r < RB; ++r) s0[r] = s1[r] = 0.f;
+#pragma unroll(RB == 4 ? 4 : 1)
   for (int k = k0; k < k0 + kc; k += 4) {
     float w0[4], w1[4];
 #pragma unroll
@@ -353,7 +357,7 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(GemmArgs g, Epi epi) {
       w1[j] = w[(int64_t)(k + j) * N + 16];
     }
 #pragma unroll
-    for (int r = 0; r < 16; ++r) {
+    for (int r = 0; r < RB; ++r) {
       // rows past R read row R-1 (their sums are never used)
       const float4 a = *reinterpret_cast<const float4*>(A + (int64_t)min(r0 + r, g.R - 1) * g.lda + k);
       s0[r] = fmaf(a.x, w0[0], s0[r]);
@@ -367,14 +371,14 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(GemmArgs g, Epi epi) {
     }
   }
 #pragma unroll
-  for (int r = 0; r < 16; ++r) {
+  for (int r = 0; r < RB; ++r) {
     red[kq][r][c] = s0[r];
     red[kq][r][16 + c] = s1[r];
   }
   __syncthreads();
   const int rr = threadIdx.x / 16;
   const int row = r0 + rr;
-  if (row >= g.R) return;
+  if (rr >= RB || row >= g.R) return;
   float t0 = 0.f, t1 = 0.f;
 #pragma unroll
   for (int q = 0; q < 16; ++q) {
@@ -931,8 +935,12 @@ void launch(const GemmArgs& g, const Epi& epi, hipStream_t s) {
     }
   }
   if (g.kind == W_F32) {
-    dim3 grid(g.NPT, (g.R + 15) / 16);
-    hipLaunchKernelGGL(gemm_f32_kernel<Epi>, grid, dim3(256), 0, s, g, epi);
+    // 16-row blocks share each weight load among more rows; 4-row blocks while
+    // the 16-row ones would leave CUs idle
+    if (g.NPT * ((g.R + 15) / 16) < 256)
+      hipLaunchKernelGGL((gemm_f32_kernel<Epi, 4>), dim3(g.NPT, (g.R + 3) / 4), dim3(256), 0, s, g, epi);
+    else
+      hipLaunchKernelGGL((gemm_f32_kernel<Epi, 16>), dim3(g.NPT, (g.R + 15) / 16), dim3(256), 0, s, g, epi);
   } else if (g.R >= 256 && g.A_lo == nullptr && g.A_ind == nullptr && g.rows_per_req == 0 && g.NPT % 4 == 0 &&
              g.kind != W_FP4) {
     const int tiles = gemm_tiles(g);

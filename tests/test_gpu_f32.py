@@ -1,0 +1,34 @@
+"""The fp32 path's attention and GEMMs at the edges of their launch rules:
+one and several key chunks (512 keys each), a last chunk that is no multiple of
+four keys, no prefix at all (the state token then sees one key), every
+head_dim, and enough rows for both GEMM block heights.  Bar: the fp32 path's
+own (1e-4), three decades above fp32 accumulation over these sums."""
+import pytest
+
+import oracle
+import workloads as wl
+from gpu_helpers import compare, run_gpu, small_cfg
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+
+
+@pytest.mark.parametrize("kw", [
+    dict(head_dim=64, prefix_cap=1100, prefix_min=455, prefix_max=1100),
+    dict(head_dim=128, n_q_heads=2, prefix_cap=520, prefix_min=461, prefix_max=463),
+    dict(head_dim=256, n_q_heads=2, prefix_cap=600, prefix_min=500, prefix_max=600, batch=2),
+    dict(head_dim=64, prefix_cap=8, prefix_min=0, prefix_max=0, horizon=5, batch=1),
+    dict(head_dim=64, batch=1, horizon=2, state_token=False),
+    dict(head_dim=64, batch=9, d_mlp=1024),
+])
+def test_fp32_path(kw):
+    import paper_2608_03682_amd as px
+    cfg = small_cfg("pi0", weight_dtype="f32", kv_dtype="f32", **kw)
+    print(f"[case] fp32 {kw}", flush=True)
+    case = wl.make_case(cfg, seed=13)
+    ex = px.Expert(cfg, case.weights)
+    gpu = run_gpu(ex, case)
+    ex.close()
+    ref = oracle.denoise(cfg, case.weights, case.prefix, case.prefix_len, case.noise, case.timesteps, case.state)
+    compare(f"fp32 {kw}", gpu, ref, cfg)
