@@ -431,26 +431,49 @@ template <typename T> EpiStore<T> store_epi(T* out, int ldo, const float* bias, 
   return e;
 }
 
-// split of the keys across blocks so that small batches still fill the chip
-int attn_splits_for(int B, int rows, int nkv, int keys, int rpb) {
-  const int base = ((rows + rpb - 1) / rpb) * B * nkv;   // blocks without a split
-  int s = (256 + base - 1) / base;
-  const int cap = (keys + 63) / 64;                     // at least one 64-key tile per split
-  if (s > cap) s = cap;
-  if (s > 16) s = 16;                                   // the merge kernel takes up to 16
-  // a few key tiles over a grid that already covers a quarter of the chip:
-  // the combine launch costs more than the split saves (vision tower, 256
-  // keys, 96 blocks: 7.0 us unsplit against 12.8 with 3 splits + combine)
-  if (cap <= 4 && base >= 64) s = 1;
-  return s < 1 ? 1 : s;
-}
-int attn_splits(int B, int rows, int nkv, int keys) {
-  return attn_splits_for(B, rows, nkv, keys, attention_rows_per_block(B, rows, nkv));
-}
-// the most splits either block height can ask for (buffers are sized with it,
-// so that forcing the other height at a later call still fits)
+// The most key splits a launch may take, with either block height: one block
+// per CU, at least one 64-key tile per split, the merge kernels' 16, and none
+// for a few tiles over a grid that covers a quarter of the chip.  Buffers, and
+// the calls that phyai_denoise_static's scratch admits, are sized with it.
 int attn_splits_max(int B, int rows, int nkv, int keys) {
-  return std::max(attn_splits_for(B, rows, nkv, keys, 64), attn_splits_for(B, rows, nkv, keys, 128));
+  int most = 1;
+  for (int rpb : {64, 128}) {
+    const int base = ((rows + rpb - 1) / rpb) * B * nkv;   // blocks without a split
+    const int tiles = (keys + 63) / 64;
+    if (tiles <= 4 && base >= 64) continue;
+    most = std::max(most, std::min({(256 + base - 1) / base, tiles, 16}));
+  }
+  return most;
+}
+
+// Split of the keys across blocks so that small batches still fill the chip.
+// A block holds two key tiles of K and V in LDS (512 D bytes), so 160 KB / 512 D
+// of them share a CU and a launch runs in rounds; a block costs its key tiles
+// plus about three more for its start, queries and output, and a split two
+// or four for merging.  Of the splits into equal runs of whole tiles the cheapest
+// is taken.  What this avoids is a last round of a few blocks (pi0 batch 8: 5
+// splits are 280 blocks on 256 CUs, the chunk 17.1 ms against 15.6 with 6 splits
+// of 128-row blocks) and a merge that buys nothing (prefix LM batch 4, 252 blocks
+// unsplit: 2.88 against 2.75 ms).
+int attn_splits(int B, int M, int rows, int nkv, int keys, int D) {
+  const int rpb = attention_rows_per_block(B, rows, nkv);
+  const int64_t base = (int64_t)((rows + rpb - 1) / rpb) * B * nkv;
+  const int tiles = (keys + 63) / 64;
+  const int64_t slots = 256 * std::max(1, 160 * 1024 / (512 * D));
+  const int merge = B * M < 256 ? 2 : 4;      // in the output projection, or a launch of its own
+  const int most = attn_splits_max(B, rows, nkv, keys);
+  int best = 1;
+  int64_t least = INT64_MAX;
+  for (int s = 1; s <= most; ++s) {
+    const int t = (tiles + s - 1) / s;
+    if (t > 0 && (tiles + t - 1) / t != s) continue;      // some splits would be empty
+    const int64_t cost = (base * s + slots - 1) / slots * (t + 3) + (s > 1 ? merge : 0);
+    if (cost < least) {
+      least = cost;
+      best = s;
+    }
+  }
+  return best;
 }
 
 // key splits of block l's attention at batch B (DiT: even blocks attend to
@@ -459,7 +482,7 @@ int attn_split_of(const phyai_expert& e, int l, int B) {
   if (e.f32) return 1;
   const int rows = e.M * (e.nq / e.nkv);
   const int keys = e.c.variant != PHYAI_VARIANT_DIT ? e.P + e.M : (l % 2 == 0 ? e.P : e.M);
-  return attn_splits(B, rows, e.nkv, keys);
+  return attn_splits(B, e.M, rows, e.nkv, keys, e.D);
 }
 
 // Whether block l's output projection merges the attention's key splits
