@@ -103,11 +103,13 @@ __global__ __launch_bounds__(256) void norm_rows_kernel(float* __restrict__ h, O
   }
 }
 
-// The same normalisation for d = 1024 with one block of 256 threads per row,
-// thread t holding the four consecutive columns 4t .. 4t+3: every load of the
-// row (h, each pending slice, the factors) is one 16-byte request per thread
-// and the normalised values leave in one store, where the scalar layout above
-// needs four of each.
+// The same normalisation with one block of 256 threads per row, thread t
+// holding the four consecutive columns 4t .. 4t+3 of each 1024 (NG groups
+// cover d): every load of the row (h, each pending slice, the factors) is one
+// 16-byte request per thread and group and the normalised values leave in one
+// store, where the scalar layout above needs four of each (batch 1, width 1024:
+// 3.4 -> 2.3 us; DiT's 17 rows of 1536 5.0 -> 3.9, prefix LM's 816 of 2048 8.8 ->
+// 7.1, its 4000 14.8 -> 9.5).
 // Columns c .. c+3 of row `row` (c a multiple of 4) with the pending residual
 // folded in and written back, as load_row_with_pending does for one column:
 // every request (the row, each slice, bias, gate) is one 16-byte load.
@@ -143,34 +145,60 @@ __device__ __forceinline__ void load_row4_with_pending(float* hr, int64_t row, i
   }
 }
 
-template <typename OutT>
+template <typename OutT, int NG>
 __global__ __launch_bounds__(256) void norm_rows_v4_kernel(float* __restrict__ h, OutT* __restrict__ n,
                                                            OutT* __restrict__ n_lo, int d, float eps, int mode,
                                                            const float* __restrict__ mul,
                                                            const float* __restrict__ shift, PendingResid pend) {
   __shared__ float scratch[4];
   const int row = blockIdx.x;
-  const int c = 4 * threadIdx.x;
-  const float4 mv = *reinterpret_cast<const float4*>(mul + c);
-  const float4 sv = shift ? *reinterpret_cast<const float4*>(shift + c) : make_float4(0.f, 0.f, 0.f, 0.f);
-  float v[4];
-  load_row4_with_pending(h + (int64_t)row * d, row, d, c, pend, v);
+  float4 mv[NG], sv[NG];
+  float v[NG][4];
+  // group g: columns 1024 g + 4 t .. + 3; past d (whole waves: d is a multiple of 256) the row is empty
+#pragma unroll
+  for (int g = 0; g < NG; ++g) {
+    const int c = 4 * threadIdx.x + 1024 * g;
+    mv[g] = sv[g] = make_float4(0.f, 0.f, 0.f, 0.f);
+    if (NG == 1 || c < d) {
+      mv[g] = *reinterpret_cast<const float4*>(mul + c);
+      if (shift) sv[g] = *reinterpret_cast<const float4*>(shift + c);
+    }
+  }
+#pragma unroll
+  for (int g = 0; g < NG; ++g) {
+    const int c = 4 * threadIdx.x + 1024 * g;
+    v[g][0] = v[g][1] = v[g][2] = v[g][3] = 0.f;
+    if (NG == 1 || c < d) load_row4_with_pending(h + (int64_t)row * d, row, d, c, pend, v[g]);
+  }
   float mu = 0.f;
-  if (mode == NORM_LN) mu = block_sum<256>(v[0] + v[1] + v[2] + v[3], scratch) / d;
+  if (mode == NORM_LN) {
+    float t = 0.f;
+#pragma unroll
+    for (int g = 0; g < NG; ++g) t += v[g][0] + v[g][1] + v[g][2] + v[g][3];
+    mu = block_sum<256>(t, scratch) / d;
+  }
   float ss = 0.f;
 #pragma unroll
-  for (int e = 0; e < 4; ++e) ss += (v[e] - mu) * (v[e] - mu);
+  for (int g = 0; g < NG; ++g)
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+      if (NG == 1 || 4 * (int)threadIdx.x + 1024 * g < d) ss += (v[g][e] - mu) * (v[g][e] - mu);
   const float r = rsqrtf(block_sum<256>(ss, scratch) / d + eps);
-  const float m4[4] = {mv.x, mv.y, mv.z, mv.w}, s4[4] = {sv.x, sv.y, sv.z, sv.w};
-  float t[4];
 #pragma unroll
-  for (int e = 0; e < 4; ++e) t[e] = (v[e] - mu) * r * (1.f + m4[e]) + s4[e];
-  ActIO<OutT>::store4(n + (int64_t)row * d + c, t);
-  if (n_lo) {
-    float lo[4];
+  for (int g = 0; g < NG; ++g) {
+    const int c = 4 * threadIdx.x + 1024 * g;
+    if (NG > 1 && c >= d) break;
+    const float m4[4] = {mv[g].x, mv[g].y, mv[g].z, mv[g].w}, s4[4] = {sv[g].x, sv[g].y, sv[g].z, sv[g].w};
+    float t[4];
 #pragma unroll
-    for (int e = 0; e < 4; ++e) lo[e] = t[e] - ActIO<OutT>::round(t[e]);
-    ActIO<OutT>::store4(n_lo + (int64_t)row * d + c, lo);
+    for (int e = 0; e < 4; ++e) t[e] = (v[g][e] - mu) * r * (1.f + m4[e]) + s4[e];
+    ActIO<OutT>::store4(n + (int64_t)row * d + c, t);
+    if (n_lo) {
+      float lo[4];
+#pragma unroll
+      for (int e = 0; e < 4; ++e) lo[e] = t[e] - ActIO<OutT>::round(t[e]);
+      ActIO<OutT>::store4(n_lo + (int64_t)row * d + c, lo);
+    }
   }
 }
 
@@ -503,7 +531,7 @@ __device__ __forceinline__ void block_sums(float (&v)[K], float (*scratch)[K]) {
   }
 }
 
-// The readout for d = 256 NG (NG <= 4) and A <= 32, RB action rows per
+// The readout for d = 256 NG (NG <= 6) and A <= 32, RB action rows per
 // block.  Every load the block needs is requested before any is used -- its
 // waves' W_out rows (wave w takes outputs w, w + 4, ..., rows past A re-read
 // row A-1 and are not stored), the final norm's factors, b_out, dt and the x
@@ -791,16 +819,20 @@ void norm_rows_bf16(float* h, bf16_t* n, bf16_t* n_lo, int R, int d, float eps, 
                     const float* shift, const PendingResid& pend, hipStream_t s) {
   // many rows: four rows per block, one per wave (fewer, fuller blocks); a
   // few rows (batch 1) keep 256 threads per row, which spreads a row's loads
-  // over four waves and measured faster there; at width 1024 each of those
-  // threads takes four consecutive columns (batch-1 norm 3.4 -> 2.3 us)
+  // over four waves and measured faster there; from width 1024 each of those
+  // threads takes four consecutive columns of each 1024
   if (R >= 256 && d % 256 == 0 && d <= 1024 && pend.n <= 8) {
     hipLaunchKernelGGL(norm_rows_wave_kernel<bf16_t>, dim3((R + 3) / 4), dim3(4 * kWave), 0, s, h, n, n_lo, R, d,
                        eps, mode, mul, shift, pend);
     return;
   }
-  if (d == 1024 && pend.n <= 8) {
-    hipLaunchKernelGGL(norm_rows_v4_kernel<bf16_t>, dim3(R), dim3(256), 0, s, h, n, n_lo, d, eps, mode, mul, shift,
-                       pend);
+  if (d % 256 == 0 && d >= 1024 && d <= 2048 && pend.n <= 8) {
+    if (d == 1024)
+      hipLaunchKernelGGL((norm_rows_v4_kernel<bf16_t, 1>), dim3(R), dim3(256), 0, s, h, n, n_lo, d, eps, mode, mul,
+                         shift, pend);
+    else
+      hipLaunchKernelGGL((norm_rows_v4_kernel<bf16_t, 2>), dim3(R), dim3(256), 0, s, h, n, n_lo, d, eps, mode, mul,
+                         shift, pend);
     return;
   }
   hipLaunchKernelGGL(norm_rows_kernel<bf16_t>, dim3(R), dim3(256), 0, s, h, n, n_lo, d, eps, mode, mul, shift, pend);
@@ -845,7 +877,10 @@ void readout_euler(const ReadoutArgs& r, hipStream_t s) {
   };
   if (r.A <= 32 && r.d == 1024) rows_kernel(std::integral_constant<int, 4>{});
   else if (r.A <= 32 && r.d == 256) rows_kernel(std::integral_constant<int, 1>{});
-  else {
+  else if (r.A <= 32 && r.d == 1536 && !r.has_next) {
+    // the DiT width: 16 rows 21 -> 8.8 us against the general kernel
+    hipLaunchKernelGGL((readout_rows_kernel<1, 6, false>), dim3(rows), dim3(256), 0, s, r);
+  } else {
     hipLaunchKernelGGL(readout_kernel, dim3(rows), dim3(256), 0, s, r);
   }
 }
