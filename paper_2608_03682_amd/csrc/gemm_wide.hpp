@@ -245,10 +245,11 @@ __device__ __forceinline__ void wide_epilogue(const GemmArgs& g, const EpiKV<bf1
       float v[4];
 #pragma unroll
       for (int j = 0; j < 4; ++j) v[j] = ok ? acc[m][t][j] : 0.f;
-      if (kv == 0) {
-        ActIO<bf16_t>::store4(e.kall + (((int64_t)b * e.nkv + h) * e.ldk + key) * e.D + i, v);
+      const int64_t lo = (kv / 2) * e.layer_stride;
+      if (kv % 2 == 0) {
+        ActIO<bf16_t>::store4(e.kall + lo + (((int64_t)b * e.nkv + h) * e.ldk + key) * e.D + i, v);
       } else {
-        bf16_t* dst = e.vt + (((int64_t)b * e.nkv + h) * e.D + i) * e.ldk + key;
+        bf16_t* dst = e.vt + lo + (((int64_t)b * e.nkv + h) * e.D + i) * e.ldk + key;
 #pragma unroll
         for (int j = 0; j < 4; ++j) dst[(int64_t)j * e.ldk] = f32_to_bf16(v[j]);
       }

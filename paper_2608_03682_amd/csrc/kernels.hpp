@@ -396,13 +396,16 @@ struct EpiQkv {
   }
 };
 
-// K|V projection of feature rows r = b*P + key (identity packing): columns
-// [0, nkv*D) are K heads, [nkv*D, 2*nkv*D) V heads, stored like EpiQkv's k/v.
+// K|V projections of feature rows r = b*P + key (identity packing) for any
+// number of layers side by side: of each layer's 2*nkv*D columns the first half
+// are K heads, the second V heads, stored like EpiQkv's k/v in that layer's key
+// range (layer_stride elements apart).
 template <typename OutT>
 struct EpiKV {
   static constexpr bool kWaveTile = false;
   OutT* kall; OutT* vt;
   int D, nkv, P, ldk;
+  int64_t layer_stride;
   struct ColPre {};
   struct Pre {};
   __device__ __forceinline__ ColPre colpre(int, int) const { return ColPre{}; }
@@ -415,8 +418,9 @@ struct EpiKV {
       const int col = 32 * p + 16 * hf + c;
       const int kv = col / (nkv * D), rem = col % (nkv * D);
       const int h = rem / D, i = rem % D;
-      if (kv == 0) ActIO<OutT>::store(kall + (((int64_t)b * nkv + h) * ldk + key) * D + i, v[hf]);
-      else ActIO<OutT>::store(vt + (((int64_t)b * nkv + h) * D + i) * ldk + key, v[hf]);
+      const int64_t lo = (kv / 2) * layer_stride;
+      if (kv % 2 == 0) ActIO<OutT>::store(kall + lo + (((int64_t)b * nkv + h) * ldk + key) * D + i, v[hf]);
+      else ActIO<OutT>::store(vt + lo + (((int64_t)b * nkv + h) * D + i) * ldk + key, v[hf]);
     }
   }
   __device__ __forceinline__ void operator()(int r, int p, int c, float a0, float a1) const {
