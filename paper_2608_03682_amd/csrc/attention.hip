@@ -571,10 +571,12 @@ __global__ __launch_bounds__(256) void attn_f32_kernel(AttnArgs a) {
 // Copy the caller's prefix K (row-major) and transpose its V into the
 // library's key ranges, for every layer, request and kv head: keys
 // 0 .. prefix_len[b]-1.  Block: 64 keys x D of one (layer, request, head).
-// Moves are 16 bytes wide (the caller's buffer permitting): K rows are copied
-// directly; V rows go through an LDS tile (rows padded by 16 bytes, which
-// keeps them aligned and spreads a column over the banks) and leave as runs
-// of consecutive keys of one V^T row.
+// Moves are 16 bytes wide: K rows are copied directly; V rows go through an LDS
+// tile (rows padded by 16 bytes, which keeps them aligned and spreads a column
+// over the banks) and leave as runs of consecutive keys of one V^T row.  Bound by HBM: 64 requests x 18 layers
+// 560 us, 3.7 TB/s (933 us with the zero keys written one at a time), 8 x 18
+// 82 us (170), 1 x 18 14 us (17.5).  128- and 256-key tiles, 64- and 128-dim
+// blocks and loads four at a time all measured slower.
 template <typename T, int D>
 __global__ __launch_bounds__(256) void prefix_relayout_kernel(RelayoutArgs r) {
   constexpr int VE = 16 / sizeof(T);           // elements per 16-byte move
@@ -592,39 +594,37 @@ __global__ __launch_bounds__(256) void prefix_relayout_kernel(RelayoutArgs r) {
   const T* vs = src + ((int64_t)l * 2 + 1) * blk + (int64_t)b * r.P * W + kvh * D;
   T* kd = static_cast<T*>(r.K) + (int64_t)l * r.layer_stride + (int64_t)grp * r.ldk * D;
   T* vd = static_cast<T*>(r.Vt) + (int64_t)l * r.layer_stride + (int64_t)grp * r.ldk * D;
+  constexpr int KC = 64 / VE;                  // 16-byte runs per V^T row of the tile
   if (blockIdx.x == 0) {
-    // keys plen+n_suffix .. round-up to 64 are read as whole tiles: keep them zero
+    // keys plen+n_suffix .. round-up to 64 are read as whole tiles: keep them
+    // zero, as runs along the keys (written a key at a time, every two bytes
+    // fell in another line, which took half of a large call's relayout)
     const int t0 = plen + r.n_suffix, t1 = (t0 + 63) / 64 * 64;
-    for (int i = threadIdx.x; i < (t1 - t0) * D; i += 256) {
-      const int kr = t0 + i / D, c = i % D;
-      kd[(int64_t)kr * D + c] = T(0);
-      vd[(int64_t)c * r.ldk + kr] = T(0);
+    const uint4 z = make_uint4(0, 0, 0, 0);
+    for (int i = threadIdx.x; i < (t1 - t0) * (D / VE); i += 256)
+      *reinterpret_cast<uint4*>(kd + (int64_t)t0 * D + (int64_t)i * VE) = z;
+    for (int i = threadIdx.x; i < (t1 - t0 + VE - 1) / VE * D; i += 256) {
+      const int k = t1 - VE * (i / D + 1);     // a run of V^T row i % D, the last ones first
+      T* dst = vd + (int64_t)(i % D) * r.ldk + k;
+      if (k >= t0) *reinterpret_cast<uint4*>(dst) = z;
+      else for (int e = t0 - k; e < VE; ++e) dst[e] = T(0);
     }
   }
   const int nk = min(64, plen - key0);
   if (nk <= 0) return;
-  // the library's ranges are allocated aligned; the caller's rows are 16-byte
-  // multiples apart, so its base decides
-  const bool vec = (reinterpret_cast<uintptr_t>(src) & 15) == 0;
+  // every base is 16-byte aligned (the entry point refuses others) and rows are
+  // 16-byte multiples; loads are unconditional (rows past the range re-read
+  // its last one)
   constexpr int CPR = D / VE;                  // 16-byte chunks per key row
   for (int i = threadIdx.x; i < 64 * CPR; i += 256) {
     const int kr = i / CPR, c = (i % CPR) * VE;
-    const int64_t so = (int64_t)(key0 + kr) * W + c;
-    if (kr < nk) {
-      if (vec) {
-        *reinterpret_cast<uint4*>(kd + (int64_t)(key0 + kr) * D + c) = *reinterpret_cast<const uint4*>(ks + so);
-        *reinterpret_cast<uint4*>(&tile[kr][c]) = *reinterpret_cast<const uint4*>(vs + so);
-      } else {
-#pragma unroll
-        for (int e = 0; e < VE; ++e) {
-          kd[(int64_t)(key0 + kr) * D + c + e] = ks[so + e];
-          tile[kr][c + e] = vs[so + e];
-        }
-      }
-    }
+    const int64_t so = (int64_t)(key0 + min(kr, nk - 1)) * W + c;
+    const uint4 vv = *reinterpret_cast<const uint4*>(vs + so);
+    const uint4 kv = *reinterpret_cast<const uint4*>(ks + so);
+    *reinterpret_cast<uint4*>(&tile[kr][c]) = vv;
+    if (kr < nk) *reinterpret_cast<uint4*>(kd + (int64_t)(key0 + kr) * D + c) = kv;
   }
   __syncthreads();
-  constexpr int KC = 64 / VE;                  // 16-byte runs per V^T row of the tile
   for (int i = threadIdx.x; i < D * KC; i += 256) {
     const int d = i / KC, k = (i % KC) * VE;
     T* dst = vd + (int64_t)d * r.ldk + key0 + k;

@@ -1,0 +1,58 @@
+"""The kernels at both ends of a denoising call: the prefix relayout (every
+remainder of a key range mod the 16-byte run, key ranges left behind by an
+earlier call) and the readout fused with the next step's embedding at four rows
+per block (a partial last block, with and without pending slices).  Bars as in the other parity tests."""
+import numpy as np
+import pytest
+
+import oracle
+import workloads as wl
+from gpu_helpers import compare, run_gpu, small_cfg, to_device
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+
+
+@pytest.mark.parametrize("kw", [
+    dict(horizon=49, batch=21),                                    # 1029 rows: one row in the last block
+    dict(horizon=50, batch=21, weight_dtype="f32", kv_dtype="f32"),
+    dict(horizon=41, batch=26, d_model=1024, action_dim=7),        # 1066 rows of width 1024: two
+    dict(horizon=41, batch=26, d_model=1024, weight_dtype="fp8"),
+])
+@pytest.mark.parametrize("variant", ["pi0", "pi05"])
+def test_readout_four_rows(variant, kw):
+    import paper_2608_03682_amd as px
+    kw = dict(kw)
+    if kw.get("weight_dtype") in ("f32", "fp8") and variant == "pi05":
+        kw.update(weight_dtype="bf16", kv_dtype="bf16", d_mlp=2048)    # K slices of the down projection
+    cfg = small_cfg(variant, n_layers=1, **kw)
+    print(f"[case] readout of four rows {variant} {kw}", flush=True)
+    case = wl.make_case(cfg, seed=5)
+    ex = px.Expert(cfg, case.weights)
+    gpu = run_gpu(ex, case)
+    ex.close()
+    ref = oracle.denoise(cfg, case.weights, case.prefix, case.prefix_len, case.noise, case.timesteps, case.state)
+    compare(f"readout of four rows {variant} {kw}", gpu, ref, cfg)
+
+
+@pytest.mark.parametrize("kw", [
+    dict(head_dim=64), dict(head_dim=256, n_q_heads=2), dict(head_dim=64, weight_dtype="f32", kv_dtype="f32"),
+])
+def test_relayout_leaves_no_stale_key(kw):
+    """An earlier call fills every key range with NaN; the next one's ranges end
+    at each remainder of a run, and their masked keys have to be zeros again."""
+    import paper_2608_03682_amd as px
+    cfg = small_cfg("pi0", batch=9, prefix_cap=130, prefix_min=40, prefix_max=130, n_steps=2, **kw)
+    print(f"[case] relayout {kw}", flush=True)
+    case = wl.make_case(cfg, seed=8)
+    case.prefix_len[:] = 64 + 13 - cfg.horizon - 1 + np.arange(9)      # key ranges end at 77 .. 85
+    case.prefix_len[8] = 77                                            # ... and at 128, a whole tile
+    prefix, noise, state = to_device(case)
+    ex = px.Expert(cfg, case.weights)
+    nan = torch.full_like(prefix, float("nan")) if prefix.is_floating_point() else torch.full_like(prefix, 0x7fc0)
+    ex.denoise(nan, np.full(9, 130, np.int32), noise, case.timesteps, state)
+    gpu = run_gpu(ex, case, dev=(prefix, noise, state))
+    ex.close()
+    ref = oracle.denoise(cfg, case.weights, case.prefix, case.prefix_len, case.noise, case.timesteps, case.state)
+    compare(f"relayout {kw}", gpu, ref, cfg)
