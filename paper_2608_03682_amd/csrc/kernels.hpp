@@ -576,9 +576,8 @@ struct ReadoutArgs {
   EmbedArgs next;
 };
 void readout_euler(const ReadoutArgs&, hipStream_t);
-// Whether readout_euler can take has_next for these sizes: only its one-row
-// blocks (the four-row form needs too many registers with the embedding).
-bool readout_fuses_embedding(int A, int d, int rows, bool pending);
+// Whether readout_euler can take has_next for these sizes.
+bool readout_fuses_embedding(int A, int d);
 
 void copy_noise_to_state(const CallDesc* desc, float* x, int64_t n, hipStream_t);
 void copy_state_to_out(const CallDesc* desc, const float* x, int64_t n, hipStream_t);

@@ -536,9 +536,10 @@ __device__ __forceinline__ void block_sums(float (&v)[K], float (*scratch)[K]) {
 // waves' W_out rows (wave w takes outputs w, w + 4, ..., rows past A re-read
 // row A-1 and are not stored), the final norm's factors, b_out, dt and the x
 // entries it updates, then the rows -- so the block makes one memory round
-// trip.  RB = 1 adds the pending split partials of the last block; RB > 1
-// (rows without them) shares each W_out load among RB rows.  Per output the
-// products are summed in the order of readout_kernel.
+// trip.  The pending split partials of the last block are added on the way.
+// RB > 1 shares each W_out and embedding weight load (256 KiB a block) among
+// RB rows.  Per output the products are summed in the order of
+// readout_kernel.
 template <int RB, int NG, bool FUSE>
 __global__ __launch_bounds__(256) void readout_rows_kernel(ReadoutArgs r) {
   constexpr int QA = 8;                      // outputs per wave
@@ -558,10 +559,9 @@ __global__ __launch_bounds__(256) void readout_rows_kernel(ReadoutArgs r) {
     for (int i = 0; i < NG; ++i)
       w4[q][i] = *reinterpret_cast<const float4*>(r.out_w + (int64_t)a * d + 4 * lane + 256 * i);
   }
-  // one row of width 1024: thread t holds columns 4t .. 4t+3 (16-byte
-  // requests for the row and each pending slice); otherwise columns
-  // t + 256 i
-  constexpr bool V4 = RB == 1 && NG == 4;
+  // width 1024: thread t holds columns 4t .. 4t+3 (16-byte requests for the
+  // rows and their pending slices); otherwise columns t + 256 i
+  constexpr bool V4 = NG == 4;
   float mv[NG], sv[NG];
   if constexpr (V4) {
     const float4 m = *reinterpret_cast<const float4*>(r.mul + 4 * threadIdx.x);
@@ -582,38 +582,71 @@ __global__ __launch_bounds__(256) void readout_rows_kernel(ReadoutArgs r) {
   const float xv = r.x[xi], bv = r.out_b[upd ? ua : 0], dtv = r.dt[0];
 
   float v[RB][NG];
-  if constexpr (V4) {
+  if constexpr (RB == 1) {
     const int b = ar0 / r.H, j = ar0 % r.H;
     const int64_t hrow = (int64_t)b * r.M + r.off + j;
-    load_row4_with_pending(r.h + hrow * d, hrow, d, 4 * threadIdx.x, r.pend, v[0]);
-  } else if constexpr (RB == 1) {
-    const int b = ar0 / r.H, j = ar0 % r.H;
-    const int64_t hrow = (int64_t)b * r.M + r.off + j;
-    float vv[kMaxPer];
-    load_row_with_pending(r.h + hrow * d, hrow, d, r.pend, vv);
+    if constexpr (V4) {
+      load_row4_with_pending(r.h + hrow * d, hrow, d, 4 * threadIdx.x, r.pend, v[0]);
+    } else {
+      float vv[kMaxPer];
+      load_row_with_pending(r.h + hrow * d, hrow, d, r.pend, vv);
 #pragma unroll
-    for (int i = 0; i < NG; ++i) v[0][i] = vv[i];
+      for (int i = 0; i < NG; ++i) v[0][i] = vv[i];
+    }
   } else {
+    // as load_row_with_pending, a slice of all rows at a time; rows past the
+    // end re-read the last one.  Nothing is written back: the next step's
+    // embedding replaces the rows.
+    int64_t hrow[RB];
 #pragma unroll
     for (int rr = 0; rr < RB; ++rr) {
       const int ar = min(ar0 + rr, nrows - 1);
-      const int b = ar / r.H, j = ar % r.H;
-      const float* hr = r.h + ((int64_t)b * r.M + r.off + j) * d;
+      hrow[rr] = (int64_t)(ar / r.H) * r.M + r.off + ar % r.H;
+    }
+    auto columns = [&](const float* p, float (&o)[NG]) {
+      if constexpr (V4) {
+        const float4 q = *reinterpret_cast<const float4*>(p + 4 * threadIdx.x);
+        o[0] = q.x; o[1] = q.y; o[2] = q.z; o[3] = q.w;
+      } else {
 #pragma unroll
-      for (int i = 0; i < NG; ++i) v[rr][i] = hr[threadIdx.x + 256 * i];
+        for (int i = 0; i < NG; ++i) o[i] = p[threadIdx.x + 256 * i];
+      }
+    };
+#pragma unroll
+    for (int rr = 0; rr < RB; ++rr) columns(r.h + hrow[rr] * d, v[rr]);
+    if (r.pend.n > 0) {
+      float t[RB][NG] = {}, bs[NG], gt[NG];
+      if (r.pend.bias) columns(r.pend.bias, bs);
+      if (r.pend.gate) columns(r.pend.gate, gt);
+      for (int sp = 0; sp < r.pend.n; ++sp) {
+        float sl[RB][NG];
+#pragma unroll
+        for (int rr = 0; rr < RB; ++rr) columns(r.pend.part + sp * r.pend.stride + hrow[rr] * d, sl[rr]);
+#pragma unroll
+        for (int rr = 0; rr < RB; ++rr)
+#pragma unroll
+          for (int i = 0; i < NG; ++i) t[rr][i] += sl[rr][i];
+      }
+#pragma unroll
+      for (int rr = 0; rr < RB; ++rr)
+#pragma unroll
+        for (int i = 0; i < NG; ++i)
+          v[rr][i] += (t[rr][i] + (r.pend.bias ? bs[i] : 0.f)) * (r.pend.gate ? gt[i] : 1.f);
     }
   }
 
   // Fused with the next step's embedding: its inputs that do not depend on
   // the update (the embedding weights for this thread's four columns, bias,
-  // row vector, position and state rows) are requested with the rows.
+  // row vector, position and state rows).  One row per block requests them
+  // with the row; several rows, once W_out's registers are free (a thread
+  // would not keep within 256 otherwise, and other blocks cover the wait).
   const EmbedArgs& e = r.next;
   const int ec = 4 * threadIdx.x;              // d <= 1024: one group of four columns
   const bool ecv = ec < d;
   const int ecc = ecv ? ec : 0;
   float4 ew[FUSE ? 32 : 1], ebias = make_float4(0.f, 0.f, 0.f, 0.f), erv = ebias;
   float4 epv[FUSE ? RB : 1], esv[FUSE ? RB : 1];
-  if constexpr (FUSE) {
+  auto request_embedding = [&] {
 #pragma unroll
     for (int a = 0; a < 32; ++a)
       ew[a] = *reinterpret_cast<const float4*>(e.in_w + (int64_t)min(a, e.A - 1) * d + ecc);
@@ -627,7 +660,8 @@ __global__ __launch_bounds__(256) void readout_rows_kernel(ReadoutArgs r) {
       esv[rr] = e.off ? *reinterpret_cast<const float4*>(e.e_state + (int64_t)b * d + ecc)
                       : make_float4(0.f, 0.f, 0.f, 0.f);
     }
-  }
+  };
+  if constexpr (FUSE && RB == 1) request_embedding();
 
   float mu[RB], st[RB];
 #pragma unroll
@@ -689,7 +723,8 @@ __global__ __launch_bounds__(256) void readout_rows_kernel(ReadoutArgs r) {
     }
   }
   __syncthreads();
-  const float xn = xv + dtv * (red[ur][ua] + bv);
+  if constexpr (FUSE && RB > 1) request_embedding();
+  const float xn = xv + dtv * (red[upd ? ur : 0][ua] + bv);
   if (upd) r.x[xi] = xn;
   if constexpr (FUSE) {
     // y = act(x_new . in_w + in_b + rowvec + pos[j]) into the next step's
@@ -855,20 +890,22 @@ void embed_state(const CallDesc* desc, const float* w, const float* b, float* e,
                  hipStream_t s) {
   hipLaunchKernelGGL(state_embed_kernel, dim3(B), dim3(256), 0, s, desc, w, b, e, A, d);
 }
-// the readout rows kernel takes four rows per block for many rows without a
-// pending residual, one otherwise
-static bool readout_four_rows(int rows, bool pending) { return !pending && rows >= 1024; }
+// The readout rows kernel takes four rows per block for many rows, where the
+// 256 KiB of weights that every block reads bound it (1600 rows of pi0.5 with two
+// pending slices 41 -> 18 us; 3200 rows 28 us, as two kernels 34), and one otherwise,
+// where more blocks in flight count.
+static bool readout_four_rows(int rows) { return rows >= 1024; }
 
-bool readout_fuses_embedding(int A, int d, int rows, bool pending) {
-  return A <= 32 && (d == 1024 || d == 256) && !readout_four_rows(rows, pending);
-}
+bool readout_fuses_embedding(int A, int d) { return A <= 32 && (d == 1024 || d == 256); }
 
 void readout_euler(const ReadoutArgs& r, hipStream_t s) {
   const int rows = r.B * r.H;
-  const bool four = readout_four_rows(rows, r.pend.n > 0);
+  const bool four = readout_four_rows(rows);
   auto rows_kernel = [&](auto ng) {
     constexpr int NG = decltype(ng)::value;
-    if (four)
+    if (four && r.has_next)
+      hipLaunchKernelGGL((readout_rows_kernel<4, NG, true>), dim3((rows + 3) / 4), dim3(256), 0, s, r);
+    else if (four)
       hipLaunchKernelGGL((readout_rows_kernel<4, NG, false>), dim3((rows + 3) / 4), dim3(256), 0, s, r);
     else if (r.has_next)
       hipLaunchKernelGGL((readout_rows_kernel<1, NG, true>), dim3(rows), dim3(256), 0, s, r);

@@ -815,7 +815,7 @@ void enqueue_loop(phyai_expert& e, int B, int K, hipStream_t s) {
     ro.eps = e.c.rms_eps;
     ro.out_w = e.out_w; ro.out_b = e.out_b; ro.dt = e.dt + k; ro.x = e.x;
     ro.pend = fold_norms(e, B) ? PendingResid{} : pending_of(e, 1, L - 1, k, B);
-    embedded = k + 1 < K && readout_fuses_embedding(e.A, d, B * H, ro.pend.n > 0);
+    embedded = k + 1 < K && readout_fuses_embedding(e.A, d);
     if (embedded) {
       ro.has_next = 1;
       ro.next = embed_args(k + 1);
