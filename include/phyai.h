@@ -326,7 +326,9 @@ int phyai_prepare(phyai_expert* e, int32_t batch, int32_t n_steps, void* stream)
 
 /* Copy the residual stream h [B*M][d] (float32) left by the last
  * phyai_denoise call (after the final step's last layer, before the final
- * norm) into `dst` (device).  Diagnostic for layer-by-layer parity tests. */
+ * norm) into `dst` (device).  State rows, which the readout does not read,
+ * lack the last layer's residual contributions that are still in K slices
+ * (small batches).  Diagnostic for layer-by-layer parity tests. */
 int phyai_debug_hidden(phyai_expert* e, float* dst, int32_t batch, void* stream);
 
 /* Measurement aid: enqueue `reps` passes over all L layers of one stage of

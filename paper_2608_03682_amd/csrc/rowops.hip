@@ -595,8 +595,9 @@ __global__ __launch_bounds__(256) void readout_rows_kernel(ReadoutArgs r) {
     }
   } else {
     // as load_row_with_pending, a slice of all rows at a time; rows past the
-    // end re-read the last one.  Nothing is written back: the next step's
-    // embedding replaces the rows.
+    // end re-read the last one.  The rows are written back after the last
+    // step only (the call leaves them to phyai_debug_hidden): before, the next
+    // step's embedding replaces them.
     int64_t hrow[RB];
 #pragma unroll
     for (int rr = 0; rr < RB; ++rr) {
@@ -632,6 +633,19 @@ __global__ __launch_bounds__(256) void readout_rows_kernel(ReadoutArgs r) {
 #pragma unroll
         for (int i = 0; i < NG; ++i)
           v[rr][i] += (t[rr][i] + (r.pend.bias ? bs[i] : 0.f)) * (r.pend.gate ? gt[i] : 1.f);
+      if constexpr (!FUSE) {
+#pragma unroll
+        for (int rr = 0; rr < RB; ++rr) {
+          if (ar0 + rr >= nrows) break;
+          float* hr = r.h + hrow[rr] * d;
+          if constexpr (V4) {
+            *reinterpret_cast<float4*>(hr + 4 * threadIdx.x) = make_float4(v[rr][0], v[rr][1], v[rr][2], v[rr][3]);
+          } else {
+#pragma unroll
+            for (int i = 0; i < NG; ++i) hr[threadIdx.x + 256 * i] = v[rr][i];
+          }
+        }
+      }
     }
   }
 

@@ -1,7 +1,8 @@
 """The kernels at both ends of a denoising call: the prefix relayout (every
 remainder of a key range mod the 16-byte run, key ranges left behind by an
 earlier call) and the readout fused with the next step's embedding at four rows
-per block (a partial last block, with and without pending slices).  Bars as in the other parity tests."""
+per block (a partial last block, with and without pending slices, and the
+residual stream it leaves).  Bars as in the other parity tests."""
 import numpy as np
 import pytest
 
@@ -34,6 +35,34 @@ def test_readout_four_rows(variant, kw):
     ex.close()
     ref = oracle.denoise(cfg, case.weights, case.prefix, case.prefix_len, case.noise, case.timesteps, case.state)
     compare(f"readout of four rows {variant} {kw}", gpu, ref, cfg)
+
+
+@pytest.mark.parametrize("variant,kw", [
+    ("pi0", dict(batch=21)), ("pi05", dict(batch=21)), ("pi0", dict(batch=21, d_model=1024, n_steps=1)),
+])
+def test_hidden_rows_after_four_row_readout(variant, kw):
+    """phyai_debug_hidden's action rows hold the last block's down projection
+    also where that is split over K and the readout adds its slices four rows
+    at a time (1,050 rows, the last block half empty): against the same requests
+    at batch 3, whose rows other kernels finish.  Without it they are off by the
+    block's MLP output, 0.1 and more; the two batches' bf16 roundings of one
+    block's operands differ by about 1e-3."""
+    import paper_2608_03682_amd as px
+    cfg = small_cfg(variant, n_layers=1, d_mlp=2048, **{"n_steps": 2, **kw})
+    print(f"[case] hidden rows {variant} {kw}", flush=True)
+    case = wl.make_case(cfg, seed=9)
+    prefix, noise, state = to_device(case)
+    ex = px.Expert(cfg, case.weights)
+
+    def hidden(n):
+        pick = slice(cfg.batch - n, cfg.batch)
+        ex.denoise(prefix[:, :, pick].contiguous(), case.prefix_len[pick], noise[pick].contiguous(), case.timesteps,
+                   None if state is None else state[pick].contiguous())
+        h = ex.debug_hidden(n).cpu().numpy().astype(np.float64).reshape(n, cfg.tokens, cfg.d_model)
+        return h[-3:, cfg.tokens - cfg.horizon:]
+
+    compare(f"hidden rows {variant} {kw}", hidden(cfg.batch), hidden(3), cfg)
+    ex.close()
 
 
 @pytest.mark.parametrize("kw", [
