@@ -504,8 +504,10 @@ __global__ __launch_bounds__(256) void attn_f32_kernel(AttnArgs a) {
 #pragma unroll
   for (int i = 0; i < kPre; ++i) vpre[i] = *reinterpret_cast<const float4*>(vrow + 4 * min(j + TPD * i, a.ldk / 4 - 1));
   const int plen = a.desc->prefix_len[b];
-  const int n_keys = (a.keys_from_prefix ? plen : 0) + a.n_suffix;
+  // the state token's query sees the prefix and its own key, the first plen + 1
+  // of the range: the rest are never read, whatever they hold
   const bool state_q = a.mask_mode == 1 && tok == 0;
+  const int n_keys = state_q ? plen + 1 : (a.keys_from_prefix ? plen : 0) + a.n_suffix;
   float m = -INFINITY, l = 0.f, acc = 0.f;
   for (int k0 = 0; k0 < n_keys; k0 += kF32Chunk) {
     const int n = min(kF32Chunk, n_keys - k0);
@@ -523,7 +525,7 @@ __global__ __launch_bounds__(256) void attn_f32_kernel(AttnArgs a) {
       }
       s += dpp_f32<0xB1>(s);                    // the key's other three lanes
       s += dpp_f32<0x4E>(s);
-      s = state_q && k0 + kk > plen ? -INFINITY : s * a.scale;
+      s *= a.scale;
       if (tid % 4 == 0) sc[kk] = s;
       mx = fmaxf(mx, s);
     }
@@ -533,7 +535,7 @@ __global__ __launch_bounds__(256) void attn_f32_kernel(AttnArgs a) {
     __syncthreads();                            // scores and wave maxima written
     mx = fmaxf(fmaxf(scratch[0], scratch[1]), fmaxf(scratch[2], scratch[3]));
     const float mn = fmaxf(m, mx);
-    if (mn == -INFINITY) {                      // every key so far masked (block-uniform)
+    if (mn == -INFINITY) {                      // no score above -inf so far (block-uniform)
       __syncthreads();
       continue;
     }

@@ -46,7 +46,7 @@ def test_hidden_rows_after_four_row_readout(variant, kw):
     at a time (1,050 rows, the last block half empty): against the same requests
     at batch 3, whose rows other kernels finish.  Without it they are off by the
     block's MLP output, 0.1 and more; the two batches' bf16 roundings of one
-    block's operands differ by about 1e-3."""
+    block's operands differ by up to 2e-3."""
     import paper_2608_03682_amd as px
     cfg = small_cfg(variant, n_layers=1, d_mlp=2048, **{"n_steps": 2, **kw})
     print(f"[case] hidden rows {variant} {kw}", flush=True)

@@ -3,11 +3,12 @@ one and several key chunks (512 keys each), a last chunk that is no multiple of
 four keys, no prefix at all (the state token then sees one key), every
 head_dim, and enough rows for both GEMM block heights.  Bar: the fp32 path's
 own (1e-4), three decades above fp32 accumulation over these sums."""
+import numpy as np
 import pytest
 
 import oracle
 import workloads as wl
-from gpu_helpers import compare, run_gpu, small_cfg
+from gpu_helpers import compare, run_gpu, small_cfg, to_device
 
 pytestmark = pytest.mark.gpu
 
@@ -32,3 +33,29 @@ def test_fp32_path(kw):
     ex.close()
     ref = oracle.denoise(cfg, case.weights, case.prefix, case.prefix_len, case.noise, case.timesteps, case.state)
     compare(f"fp32 {kw}", gpu, ref, cfg)
+
+
+def _hidden(ex, dev, case, batch):
+    prefix, noise, state = dev
+    ex.denoise(prefix, case.prefix_len, noise, case.timesteps, state)
+    return ex.debug_hidden(batch).cpu().numpy()
+
+
+@pytest.mark.parametrize("plen", [70, 600])
+def test_fp32_state_token_never_reads_masked_keys(plen):
+    """The state token sees the prefix and itself, so its row of the residual
+    stream stays bit for bit the same when the other suffix tokens (and with
+    them their keys and values) are infinite or NaN."""
+    import paper_2608_03682_amd as px
+    cfg = small_cfg("pi0", weight_dtype="f32", kv_dtype="f32", n_layers=1, n_steps=1, batch=1, prefix_cap=600)
+    print(f"[case] fp32 masked keys, prefix {plen}", flush=True)
+    case = wl.make_case(cfg, seed=14)
+    case.prefix_len[:] = plen
+    prefix, noise, state = to_device(case)
+    ex = px.Expert(cfg, case.weights)
+    ref = _hidden(ex, (prefix, noise, state), case, 1)[0]
+    assert np.isfinite(ref).all()
+    for bad in (float("inf"), float("nan")):
+        noise[0, 3] = bad
+        np.testing.assert_array_equal(_hidden(ex, (prefix, noise, state), case, 1)[0], ref)
+    ex.close()
