@@ -535,10 +535,6 @@ __global__ __launch_bounds__(256) void attn_f32_kernel(AttnArgs a) {
     __syncthreads();                            // scores and wave maxima written
     mx = fmaxf(fmaxf(scratch[0], scratch[1]), fmaxf(scratch[2], scratch[3]));
     const float mn = fmaxf(m, mx);
-    if (mn == -INFINITY) {                      // no score above -inf so far (block-uniform)
-      __syncthreads();
-      continue;
-    }
     const float al = __expf(m - mn);
     float ps = 0.f;
     for (int kk = tid; kk < n; kk += 256) {

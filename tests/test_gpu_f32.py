@@ -59,3 +59,24 @@ def test_fp32_state_token_never_reads_masked_keys(plen):
         noise[0, 3] = bad
         np.testing.assert_array_equal(_hidden(ex, (prefix, noise, state), case, 1)[0], ref)
     ex.close()
+
+
+@pytest.mark.parametrize("first,last", [(0, 1), (0, 512), (512, 600)])
+def test_fp32_nan_keys_are_not_skipped(first, last):
+    """NaN among the keys spoils every softmax that covers them, wherever they
+    lie among the chunks of 512 and also where a chunk holds nothing else: each
+    such query's attention is replaced by zeros, as with one NaN key at 40."""
+    import paper_2608_03682_amd as px
+    cfg = small_cfg("pi0", weight_dtype="f32", kv_dtype="f32", n_layers=1, n_steps=1, batch=1, prefix_cap=600)
+    print(f"[case] fp32 NaN keys {first}..{last}", flush=True)
+    case = wl.make_case(cfg, seed=15)
+    case.prefix_len[:] = 600
+    prefix, noise, state = to_device(case)
+    ex = px.Expert(cfg, case.weights)
+    one, many = prefix.clone(), prefix.clone()
+    one[:, 0, :, 40] = float("nan")
+    many[:, 0, :, first:last] = float("nan")
+    ref = _hidden(ex, (one, noise, state), case, 1)
+    assert np.isfinite(ref).all()
+    np.testing.assert_array_equal(_hidden(ex, (many, noise, state), case, 1), ref)
+    ex.close()
