@@ -993,7 +993,10 @@ void launch(const GemmArgs& g, const Epi& epi, hipStream_t s) {
 void gemm_store_bf16(const GemmArgs& g, const EpiStore<bf16_t>& e, hipStream_t s) { launch(g, e, s); }
 void gemm_store_f32(const GemmArgs& g, const EpiStore<float>& e, hipStream_t s) { launch(g, e, s); }
 void gemm_resid(const GemmArgs& g, const EpiResid& e, hipStream_t s) { launch(g, e, s); }
-void gemm_geglu_bf16(const GemmArgs& g, const EpiGeglu<bf16_t>& e, hipStream_t s) { launch(g, e, s); }
+void gemm_geglu_bf16(const GemmArgs& g, const EpiGeglu<bf16_t>& e, hipStream_t s) {
+  if (e.lo) launch(g, EpiGegluLo{e}, s);
+  else launch(g, e, s);
+}
 void gemm_geglu_f32(const GemmArgs& g, const EpiGeglu<float>& e, hipStream_t s) { launch(g, e, s); }
 void gemm_qkv_bf16(const GemmArgs& g, const EpiQkv<bf16_t>& e, hipStream_t s) { launch(g, e, s); }
 void gemm_qkv_f32(const GemmArgs& g, const EpiQkv<float>& e, hipStream_t s) { launch(g, e, s); }

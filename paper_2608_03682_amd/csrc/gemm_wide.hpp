@@ -68,7 +68,7 @@ __device__ __forceinline__ void wide_store(const GemmArgs& g, const EpiStore<Out
       for (int t = 0; t < 2; ++t)
 #pragma unroll
         for (int i = 0; i < 4; ++i)
-          v[t][i] = apply_act(ACT, acc[m][2 * pp + t][i] + b[2 * pp + t][i] + rv[2 * pp + t][i]);
+          v[t][i] = apply_act<OutT>(ACT, acc[m][2 * pp + t][i] + b[2 * pp + t][i] + rv[2 * pp + t][i]);
       if constexpr (std::is_same<OutT, float>::value) {
         ActIO<OutT>::store4(o + 32 * pp + 4 * lg, v[0]);
         ActIO<OutT>::store4(o + 32 * pp + 16 + 4 * lg, v[1]);
@@ -123,9 +123,9 @@ __device__ __forceinline__ void wide_epilogue(const GemmArgs& g, const EpiResid&
   }
 }
 
-template <int MT>
-__device__ __forceinline__ void wide_epilogue(const GemmArgs& g, const EpiGeglu<bf16_t>& e, f32x4 (&acc)[MT][4],
-                                              int row0, int p0, int lr, int lg, bf16_t*) {
+template <bool LO, int MT>
+__device__ __forceinline__ void wide_geglu(const GemmArgs& g, const EpiGeglu<bf16_t>& e, f32x4 (&acc)[MT][4], int row0,
+                                           int p0, int lr, int lg) {
 #pragma unroll
   for (int m = 0; m < MT; ++m) {
     const int row = row0 + 16 * m + lr;
@@ -135,13 +135,20 @@ __device__ __forceinline__ void wide_epilogue(const GemmArgs& g, const EpiGeglu<
     for (int pp = 0; pp < 2; ++pp)
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
-        v[pp][i] = gelu_tanh_f(acc[m][2 * pp][i]) * acc[m][2 * pp + 1][i];
+        const float z = acc[m][2 * pp][i];
+        v[pp][i] = (LO ? gelu_tanh_f(z) : gelu_tanh_bf16(z)) * acc[m][2 * pp + 1][i];
         lo[pp][i] = v[pp][i] - ActIO<bf16_t>::round(v[pp][i]);
       }
     const int64_t o = (int64_t)row * e.ldo + 16 * (p0 + lg % 2) + 8 * (lg / 2);
     *reinterpret_cast<uint4*>(e.out + o) = join_halves(v[0], v[1]);
-    if (e.lo) *reinterpret_cast<uint4*>(e.lo + o) = join_halves(lo[0], lo[1]);
+    if constexpr (LO) *reinterpret_cast<uint4*>(e.lo + o) = join_halves(lo[0], lo[1]);
   }
+}
+template <int MT>
+__device__ __forceinline__ void wide_epilogue(const GemmArgs& g, const EpiGeglu<bf16_t>& e, f32x4 (&acc)[MT][4],
+                                              int row0, int p0, int lr, int lg, bf16_t*) {
+  if (e.lo) wide_geglu<true>(g, e, acc, row0, p0, lr, lg);
+  else wide_geglu<false>(g, e, acc, row0, p0, lr, lg);
 }
 
 // A wave's 64 columns lie in one head, so whether they are Q, K or V is known

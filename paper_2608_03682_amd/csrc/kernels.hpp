@@ -124,7 +124,7 @@ struct EpiStore {
       float t = v[hf];
       if (bias) t += q.b[hf];
       if (rowvec) t += q.rv[hf];
-      ActIO<OutT>::store(out + (int64_t)orow * ldo + col, apply_act(act, t));
+      ActIO<OutT>::store(out + (int64_t)orow * ldo + col, apply_act<OutT>(act, t));
     }
   }
   __device__ __forceinline__ void operator()(int r, int p, int c, float a0, float a1) const {
@@ -173,8 +173,8 @@ struct EpiResid {
 };
 
 // pair tile p holds gate column 16p+c (half 0) and up column 16p+c (half 1).
-// With `lo` set (bf16 only) the rounding residue is stored there, so that
-// out + lo carries about 16 significant bits into the next GEMM.
+// With `lo` set (bf16 only; EpiGegluLo) the rounding residue is stored there, so
+// that out + lo carries about 16 significant bits into the next GEMM.
 template <typename OutT>
 struct EpiGeglu {
   static constexpr bool kWaveTile = false;
@@ -185,10 +185,20 @@ struct EpiGeglu {
   __device__ __forceinline__ ColPre colpre(int, int) const { return ColPre{}; }
   __device__ __forceinline__ Pre pre(int, int, int) const { return Pre{}; }
   __device__ __forceinline__ void apply(int r, int p, int c, const ColPre&, const Pre&, float a0, float a1) const {
+    ActIO<OutT>::store(out + (int64_t)r * ldo + 16 * p + c, apply_act<OutT>(ACT_GELU, a0) * a1);
+  }
+  __device__ __forceinline__ void operator()(int r, int p, int c, float a0, float a1) const {
+    apply(r, p, c, ColPre{}, Pre{}, a0, a1);
+  }
+};
+// The same with `lo`: a type of its own, so that the form of the GELU is known
+// where the kernel is compiled.
+struct EpiGegluLo : EpiGeglu<bf16_t> {
+  __device__ __forceinline__ void apply(int r, int p, int c, const ColPre&, const Pre&, float a0, float a1) const {
     const float v = gelu_tanh_f(a0) * a1;
     const int64_t i = (int64_t)r * ldo + 16 * p + c;
-    ActIO<OutT>::store(out + i, v);
-    if (lo) ActIO<OutT>::store(lo + i, v - ActIO<OutT>::round(v));
+    ActIO<bf16_t>::store(out + i, v);
+    ActIO<bf16_t>::store(lo + i, v - ActIO<bf16_t>::round(v));
   }
   __device__ __forceinline__ void operator()(int r, int p, int c, float a0, float a1) const {
     apply(r, p, c, ColPre{}, Pre{}, a0, a1);

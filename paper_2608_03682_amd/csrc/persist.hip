@@ -761,7 +761,7 @@ __device__ __attribute__((noinline)) void phase_gateup(const PersistArgs* pa, in
     const int tok = 16 * w + 4 * (lane / 16) + v;
     if (tok >= p.M) continue;
     const float gate = fin[0][v] * rr[tok], up = fin[1][v] * rr[tok];
-    st2(go, (tok * p.F + 16 * b + lane % 16) * 2, f32_to_bf16(gelu_tanh_f(gate) * up));
+    st2(go, (tok * p.F + 16 * b + lane % 16) * 2, f32_to_bf16(gelu_tanh_bf16(gate) * up));
   }
 }
 

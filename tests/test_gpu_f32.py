@@ -35,6 +35,43 @@ def test_fp32_path(kw):
     compare(f"fp32 {kw}", gpu, ref, cfg)
 
 
+@pytest.mark.parametrize("lo,hi", [(0.0, 1.0), (1.0, 4.0), (-0.5, 0.0), (-4.0, -0.5)])
+def test_fp32_gelu_is_as_accurate_as_its_tanh_form(lo, hi):
+    """A DiT block on a zero residual stream whose MLP-in is its bias z, MLP-out
+    the identity and gate 1 leaves gelu(z) itself in every row: its error against
+    64 bits is no larger than that of z/2 (1 + tanh u) in 32-bit steps with a
+    correctly rounded tanh, in the rms over 1,024 values (known to 2 %) and, within
+    a tenth, at the worst of them."""
+    import paper_2608_03682_amd as px
+    cfg = small_cfg("dit", weight_dtype="f32", kv_dtype="f32", n_layers=1, n_steps=1, batch=1, d_model=1024,
+                    d_mlp=1024, horizon=2, n_q_heads=8, n_kv_heads=8)
+    print(f"[case] fp32 gelu {lo} .. {hi}", flush=True)
+    d, p = cfg.d_model, "layers.0."
+    z = np.random.default_rng(16).uniform(lo, hi, d).astype(np.float32)
+    zero = {k: np.zeros(s) for k, s in wl.weight_specs(cfg).items()
+            if k in ("in_w", "in_b", "state_w", "state_b", "pos_emb") or k in (p + "wo", p + "ada_w", p + "mlp_w1",
+                                                                               p + "mlp_b2")}
+    gates = np.zeros((1, 6 * d))
+    gates[0, 5 * d:] = 1.0                        # shift, scale and gate of the two halves: the MLP's gate
+    case = wl.make_case(cfg, seed=16, weights=wl.make_weights(cfg, 16, overrides={
+        **zero, p + "ada_b": gates, p + "mlp_b1": z, p + "mlp_w2": np.eye(d)}))
+    ex = px.Expert(cfg, case.weights)
+    h = _hidden(ex, to_device(case), case, 1)
+    ex.close()
+    assert (h == h[0]).all()
+    t = z.astype(np.float64)
+    u = np.sqrt(2 / np.pi) * (t + 0.044715 * t ** 3)
+    ref = t / (1 + np.exp(-2 * u))
+    f = np.float32
+    u32 = f(0.7978845608028654) * (z + f(0.044715) * z * z * z)
+    tanh_form = f(0.5) * z * (f(1) + np.tanh(u32.astype(np.float64)).astype(f))
+    rel = [np.abs(y.astype(np.float64) - ref) / np.abs(ref) for y in (h[0], tanh_form)]
+    rms, worst = [np.sqrt((e ** 2).mean()) for e in rel], [e.max() for e in rel]
+    print(f"[parity] fp32 gelu {lo} .. {hi}: rms {rms[0]:.2e} (tanh form {rms[1]:.2e}), worst {worst[0]:.2e} "
+          f"({worst[1]:.2e})", flush=True)
+    assert rms[0] <= rms[1] and worst[0] <= 1.1 * worst[1]
+
+
 def _hidden(ex, dev, case, batch):
     prefix, noise, state = dev
     ex.denoise(prefix, case.prefix_len, noise, case.timesteps, state)
