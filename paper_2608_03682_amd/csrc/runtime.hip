@@ -525,6 +525,7 @@ bool fold_norms(const phyai_expert& e, int B) {
   const char* f = getenv("PHYAI_NORM_FOLD");
   if (!f || f[0] != '1') return false;
   const int R = B * e.M;
+  if (R >= 256) return false;                 // the many-row GEMMs neither finish tiles nor scale rows
   if ((int64_t)(e.d / 32) * ((R + 15) / 16) > kFinCounters) return false;
   for (int l = 0; l < e.L; ++l)
     if (resid_split(e, 0, l, B) <= 1 || resid_split(e, 1, l, B) <= 1) return false;

@@ -281,3 +281,20 @@ def test_folded_norms_match_oracle_and_norm_kernels(name, kw):
     ex2.close()
     compare(f"norm kernels {name}", plain, ref, cfg)
     assert not np.array_equal(folded, plain), "the two paths should differ in rounding"
+
+
+def test_folded_norms_stay_off_for_many_rows():
+    """PHYAI_NORM_FOLD=1 at 408 rows, where every residual GEMM is split over K
+    too, but the many-row GEMMs run, which cannot fold: bit for bit the call
+    without the switch."""
+    cfg = small_cfg("pi0", head_dim=128, batch=8, d_mlp=1024)
+    print("[case] folded norms, 408 rows", flush=True)
+    case = wl.make_case(cfg, seed=12)
+    plain = run_gpu(_expert(cfg, case), case)
+    compare("norm kernels, 408 rows", plain, _oracle(cfg, case), cfg)
+    os.environ["PHYAI_NORM_FOLD"] = "1"
+    try:
+        folded = run_gpu(_expert(cfg, case), case)
+    finally:
+        del os.environ["PHYAI_NORM_FOLD"]
+    assert np.array_equal(folded, plain)
