@@ -917,19 +917,28 @@ WideTile wide_tile(const GemmArgs& g) {
   return best;
 }
 
+// The epilogues of the 256-column kernel.
 template <class Epi> struct WideEpi : std::true_type {};
 template <> struct WideEpi<EpiGeglu<float>> : std::false_type {};
 template <> struct WideEpi<EpiQkv<float>> : std::false_type {};
 template <> struct WideEpi<EpiKV<float>> : std::false_type {};
+// ... and of these the ones it is built for with a second operand term
+template <class Epi> struct WideTwoTerm : std::false_type {};
+template <> struct WideTwoTerm<EpiResid> : std::true_type {};
+template <> struct WideTwoTerm<EpiGeglu<bf16_t>> : std::true_type {};
+template <> struct WideTwoTerm<EpiGegluLo> : std::true_type {};
+template <> struct WideTwoTerm<EpiQkv<bf16_t>> : std::true_type {};
 
 template <class Epi>
 void launch(const GemmArgs& g, const Epi& epi, hipStream_t s) {
+  // only the small-row kernel scales rows and finishes split tiles
+  const bool many = g.row_ss == nullptr && g.fin_ctr == nullptr;
   if constexpr (WideEpi<Epi>::value) {
     const WideTile t = wide_tile(g);
     // a K split without a second operand term keeps the 128 x 128 ring: its few
     // tiles (768 x 4096 x 1024, 816 x 16384 x 2048) pay for the wide blocks' weight
     // re-reads (tower 1.90 against 1.95 ms, prefix LM 0.87 against 0.95)
-    if (t.mt > 0 && !(g.split_out && !g.A_lo)) {
+    if (many && t.mt > 0 && (g.A_lo ? WideTwoTerm<Epi>::value : !g.split_out)) {
       gemm_wide(g, epi, t, s);
       return;
     }
@@ -941,7 +950,7 @@ void launch(const GemmArgs& g, const Epi& epi, hipStream_t s) {
       hipLaunchKernelGGL((gemm_f32_kernel<Epi, 4>), dim3(g.NPT, (g.R + 3) / 4), dim3(256), 0, s, g, epi);
     else
       hipLaunchKernelGGL((gemm_f32_kernel<Epi, 16>), dim3(g.NPT, (g.R + 15) / 16), dim3(256), 0, s, g, epi);
-  } else if (g.R >= 256 && g.A_lo == nullptr && g.A_ind == nullptr && g.rows_per_req == 0 && g.NPT % 4 == 0 &&
+  } else if (many && g.R >= 256 && g.A_lo == nullptr && g.A_ind == nullptr && g.rows_per_req == 0 && g.NPT % 4 == 0 &&
              g.kind != W_FP4) {
     const int tiles = gemm_tiles(g);
     const char* force = getenv("PHYAI_GEMM_TILE");   // tests: "ring" / "deep" (read at enqueue time)
