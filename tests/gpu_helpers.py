@@ -65,3 +65,21 @@ def compare(name, gpu, ref, cfg):
     assert np.isfinite(gpu).all(), f"{name}: non-finite GPU output"
     assert err.max() <= bar, f"{name}: max abs error {err.max():.3e} > {bar:.3e}"
     return err.max()
+
+
+def cross_case(cfg, seed):
+    """A DiT case whose actions hang on every cross block's keys and values: gates
+    of 1 and larger K, V and O weights in the even layers.  (With the synthetic
+    weights as they are, a second cross block that read the first one's keys and
+    values would move the actions by 7e-4 only.)"""
+    rng = np.random.default_rng(seed)
+    d, qd, ov = cfg.d_model, cfg.n_q_heads * cfg.head_dim, {}
+    for l in range(cfg.n_layers):
+        gates = np.zeros((1, 6 * d))
+        gates[0, 2 * d:3 * d] = gates[0, 5 * d:] = 1.0
+        ov[f"layers.{l}.ada_b"] = gates
+        if l % 2 == 0:
+            for k in ("wk", "wv"):
+                ov[f"layers.{l}.{k}"] = 0.1 * rng.standard_normal((cfg.d_feat, qd))
+            ov[f"layers.{l}.wo"] = 0.1 * rng.standard_normal((qd, d))
+    return wl.make_case(cfg, seed=seed, weights=wl.make_weights(cfg, seed, overrides=ov))

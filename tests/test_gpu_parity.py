@@ -10,7 +10,7 @@ import pytest
 
 import oracle
 import workloads as wl
-from gpu_helpers import compare, run_gpu, small_cfg, to_device
+from gpu_helpers import compare, cross_case, run_gpu, small_cfg, to_device, tolerance
 
 pytestmark = pytest.mark.gpu
 
@@ -200,12 +200,12 @@ def test_small_row_gemm_row_blocks(variant, kw, mt):
 
 
 @pytest.mark.parametrize("wdt", ["bf16", "fp8"])
-@pytest.mark.parametrize("tile", ["ring", "deep", "strided"])
+@pytest.mark.parametrize("tile", ["ring", "deep"])
 def test_many_row_gemm_tiles(tile, wdt):
-    """Each many-row GEMM kernel, forced in turn for every projection: 357
-    rows (a ragged last row tile), QKV 512 columns, GeGLU 2 x 512, output and
-    down projections 256 columns.  "deep" (the four-stage ring) leaves the
-    QKV projection on the two-stage ring."""
+    """Each 128 x 128 many-row GEMM kernel, forced in turn for every projection
+    (test_gpu_wide.py has the 256-column one): 357 rows (a ragged last row tile),
+    QKV 512 columns, GeGLU 2 x 512, output and down projections 256 columns.
+    "deep" (the four-stage ring) leaves the QKV projection on the two-stage ring."""
     cfg = small_cfg("pi0", n_q_heads=6, batch=7, weight_dtype=wdt)
     print(f"[case] gemm tile {tile} {wdt}", flush=True)
     case = wl.make_case(cfg, seed=4)
@@ -298,3 +298,35 @@ def test_folded_norms_stay_off_for_many_rows():
     finally:
         del os.environ["PHYAI_NORM_FOLD"]
     assert np.array_equal(folded, plain)
+
+
+@pytest.mark.parametrize("wdt", ["bf16", "fp8", "fp4", "f32"])
+def test_dit_keys_of_several_cross_blocks(wdt):
+    """The DiT K/V projection writes every cross block's key range in one GEMM:
+    four layers (two cross blocks), 80 feature rows (the small-row and fp32
+    kernels; test_gpu_wide.py has the many-row one).  In the oracle, the second
+    block with the first one's K or V weights moves the actions past the bar."""
+    cfg = small_cfg("dit", n_layers=4, weight_dtype=wdt, kv_dtype="f32" if wdt == "f32" else "bf16")
+    print(f"[case] dit, two cross blocks {wdt}", flush=True)
+    case = cross_case(cfg, 17)
+    ref = _oracle(cfg, case)
+    compare(f"dit, two cross blocks {wdt}", run_gpu(_expert(cfg, case), case), ref, cfg)
+    for k in ("wk", "wv"):
+        wrong = {**case.weights, "layers.2." + k: case.weights["layers.0." + k]}
+        off = np.abs(_oracle(cfg, dataclasses.replace(case, weights=wrong)) - ref).max()
+        assert off > 2 * tolerance(cfg) * max(1.0, float(np.sqrt(np.mean(ref ** 2)))), (k, off)
+
+
+@pytest.mark.parametrize("variant,kw", [
+    ("pi0", dict(batch=1)), ("pi0", dict(batch=6)), ("pi05", dict(batch=2)), ("dit", {}),
+])
+@pytest.mark.parametrize("d", [1280, 1792])
+def test_widths_that_leave_waves_without_columns(variant, kw, d):
+    """Widths between 1,024 and 2,048 that are no multiple of 1,024: the norms
+    hold four columns per thread of each 1,024, so the last one or three waves
+    have none in the second group.  With and without split residuals, second
+    bf16 terms (pi0.5) and LayerNorm (DiT)."""
+    cfg = small_cfg(variant, d_model=d, time_dim=256, **kw)
+    print(f"[case] width {d} {variant} {kw}", flush=True)
+    case = wl.make_case(cfg, seed=18)
+    compare(f"width {d} {variant} {kw}", run_gpu(_expert(cfg, case), case), _oracle(cfg, case), cfg)

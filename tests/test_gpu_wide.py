@@ -1,7 +1,7 @@
 """The 256-column many-row GEMM through the C ABI: every tile height and both
 pipeline depths, at shapes that leave a ragged last row tile (R not a multiple
-of any of them), more and fewer column tiles than one band, K of four k-blocks
-and of 16, and each epilogue (QKV with and without RoPE and bias, K|V of the DiT
+of any of them), more and fewer column tiles than one band, K of 4 to 7 k-blocks
+(every way the four-stage pipeline ends) and of 16, and each epilogue (QKV with and without RoPE and bias, K|V of the DiT
 features with invalid rows, GeGLU with and without a second term, GELU, plain
 stores, residual adds, K slices).  The bars are those of the other parity tests:
 the operands are rounded to bf16 once per stage whatever the kernel."""
@@ -12,7 +12,7 @@ import pytest
 
 import oracle
 import workloads as wl
-from gpu_helpers import compare, run_gpu, small_cfg
+from gpu_helpers import compare, cross_case, run_gpu, small_cfg
 
 pytestmark = pytest.mark.gpu
 
@@ -46,6 +46,40 @@ def test_wide_gemm_expert(tile, variant, kw):
     ex.close()
     ref = oracle.denoise(cfg, case.weights, case.prefix, case.prefix_len, case.noise, case.timesteps, case.state)
     compare(f"wide tile {tile} {variant} {kw}", gpu, ref, cfg)
+
+
+@pytest.mark.parametrize("tile", TILES, indirect=True)
+@pytest.mark.parametrize("wdt", ["bf16", "fp8"])
+def test_wide_gemm_keys_of_several_cross_blocks(tile, wdt):
+    """As test_dit_keys_of_several_cross_blocks, 450 feature rows."""
+    import paper_2608_03682_amd as px
+    cfg = small_cfg("dit", n_layers=4, weight_dtype=wdt, batch=5, prefix_cap=90, prefix_min=31, prefix_max=90)
+    print(f"[case] wide tile {tile} dit, two cross blocks {wdt}", flush=True)
+    case = cross_case(cfg, 17)
+    ex = px.Expert(cfg, case.weights)
+    gpu = run_gpu(ex, case)
+    ex.close()
+    ref = oracle.denoise(cfg, case.weights, case.prefix, case.prefix_len, case.noise, case.timesteps, case.state)
+    compare(f"wide tile {tile} dit, two cross blocks {wdt}", gpu, ref, cfg)
+
+
+@pytest.mark.parametrize("tile", TILES[:3], indirect=True)
+@pytest.mark.parametrize("variant,wdt", [("pi0", "bf16"), ("pi0", "fp8"), ("pi05", "bf16")])
+@pytest.mark.parametrize("kb", [5, 6, 7])
+def test_wide_gemm_pipeline_tails(tile, variant, wdt, kb):
+    """The four-stage pipeline ends with 3, 4, 5 or 6 k-blocks left: 5, 6 and 7
+    k-blocks in the output projection (heads of 64; pi0) and in the down
+    projection (with a second operand term in pi0.5)."""
+    import paper_2608_03682_amd as px
+    kw = dict(n_q_heads=kb) if variant == "pi0" else {}
+    cfg = small_cfg(variant, batch=7, d_mlp=64 * kb, weight_dtype=wdt, **kw)
+    print(f"[case] wide tile {tile} {variant} {wdt} {kb} k-blocks", flush=True)
+    case = wl.make_case(cfg, seed=19)
+    ex = px.Expert(cfg, case.weights)
+    gpu = run_gpu(ex, case)
+    ex.close()
+    ref = oracle.denoise(cfg, case.weights, case.prefix, case.prefix_len, case.noise, case.timesteps, case.state)
+    compare(f"wide tile {tile} {variant} {wdt} {kb} k-blocks", gpu, ref, cfg)
 
 
 @pytest.mark.parametrize("tile", TILES, indirect=True)
