@@ -471,20 +471,20 @@ __global__ __launch_bounds__(256) void attn_combine_kernel(AttnArgs a) {
   *reinterpret_cast<uint2*>(op) = w;
 }
 
-// fp32 path: one block per (request, token, query head), keys in chunks of
-// kF32Chunk with an online softmax between chunks.  Within a chunk four lanes
-// share a key's score (64 keys at a time), and 256 / D lanes share an output
-// dimension, each summing every (256 / D)-th group of four keys of its V^T
-// row.  A call of a few blocks is bound by its round trips, so the first
+// fp32 path: one block of NT threads per (request, token, query head), keys in
+// chunks of kF32Chunk with an online softmax between chunks.  Within a chunk
+// four lanes share a key's score (NT / 4 keys at a time), and NT / D lanes share
+// an output dimension, each summing every (NT / D)-th group of four keys of its
+// V^T row.  A call of a few blocks is bound by its round trips, so the first
 // kPre groups of V are requested with Q and K (tiny expert, 80 keys of 64:
 // 30.6 us as one wave per row walking the keys,
 // 4.1 us this way).
 constexpr int kF32Chunk = 512;
-template <int D>
-__global__ __launch_bounds__(256) void attn_f32_kernel(AttnArgs a) {
+template <int D, int NT>
+__global__ __launch_bounds__(NT) void attn_f32_kernel(AttnArgs a) {
   __shared__ float sc[kF32Chunk];
-  __shared__ float scratch[4];
-  constexpr int TPD = 256 / D;                  // lanes per output dimension
+  __shared__ float scratch[NT / kWave];
+  constexpr int TPD = NT / D;                   // lanes per output dimension
   constexpr int QV = D / 16;                    // float4 of a key per lane
   constexpr int kPre = 6;
   const int tid = threadIdx.x;
@@ -512,7 +512,7 @@ __global__ __launch_bounds__(256) void attn_f32_kernel(AttnArgs a) {
   for (int k0 = 0; k0 < n_keys; k0 += kF32Chunk) {
     const int n = min(kF32Chunk, n_keys - k0);
     float mx = -INFINITY;
-    for (int kk = tid / 4; kk < n; kk += 64) {
+    for (int kk = tid / 4; kk < n; kk += NT / 4) {
       const float* kr = Kb + (int64_t)(k0 + kk) * D;
       float s = 0.f;
 #pragma unroll
@@ -530,19 +530,20 @@ __global__ __launch_bounds__(256) void attn_f32_kernel(AttnArgs a) {
       mx = fmaxf(mx, s);
     }
 #pragma unroll
-    for (int o = 32; o > 0; o >>= 1) mx = fmaxf(mx, __shfl_xor(mx, o, 64));
+    for (int o = 32; o > 2; o >>= 1) mx = fmaxf(mx, __shfl_xor(mx, o, 64));   // a key's four lanes agree
     if (tid % 64 == 0) scratch[tid / 64] = mx;
     __syncthreads();                            // scores and wave maxima written
-    mx = fmaxf(fmaxf(scratch[0], scratch[1]), fmaxf(scratch[2], scratch[3]));
-    const float mn = fmaxf(m, mx);
+    float mn = m;
+#pragma unroll
+    for (int i = 0; i < NT / kWave; ++i) mn = fmaxf(mn, scratch[i]);
     const float al = __expf(m - mn);
     float ps = 0.f;
-    for (int kk = tid; kk < n; kk += 256) {
+    for (int kk = tid; kk < n; kk += NT) {
       const float p = __expf(sc[kk] - mn);
       sc[kk] = p;
       ps += p;
     }
-    l = l * al + block_sum<256>(ps, scratch);   // its barriers also publish the probabilities
+    l = l * al + block_sum<NT>(ps, scratch);   // its barriers also publish the probabilities
     acc *= al;
     m = mn;
     const int n4 = n / 4;
@@ -559,7 +560,7 @@ __global__ __launch_bounds__(256) void attn_f32_kernel(AttnArgs a) {
       acc = fmaf(sc[4 * g], v.x, fmaf(sc[4 * g + 1], v.y, fmaf(sc[4 * g + 2], v.z, fmaf(sc[4 * g + 3], v.w, acc))));
     }
     for (int kk = 4 * n4 + j; kk < n; kk += TPD) acc = fmaf(sc[kk], vrow[k0 + kk], acc);
-    __syncthreads();                            // the chunk is consumed
+    if (k0 + kF32Chunk < n_keys) __syncthreads();   // the chunk is consumed before the next one's scores
   }
 #pragma unroll
   for (int o = 1; o < TPD; o <<= 1) acc += __shfl_xor(acc, o, 64);
@@ -768,9 +769,15 @@ void attention_bf16(const AttnArgs& a0, hipStream_t s) {
 
 void attention_f32(const AttnArgs& a, hipStream_t s) {
   dim3 grid(a.B * a.M, a.nq);
-  if (a.D == 64) hipLaunchKernelGGL(attn_f32_kernel<64>, grid, dim3(256), 0, s, a);
-  else if (a.D == 128) hipLaunchKernelGGL(attn_f32_kernel<128>, grid, dim3(256), 0, s, a);
-  else if (a.D == 256) hipLaunchKernelGGL(attn_f32_kernel<256>, grid, dim3(256), 0, s, a);
+  // up to 32 keys D threads (one per output dimension) are enough and leave room
+  // for more blocks (24 keys, 2,304 rows 704 -> 630 us a call of two layers and
+  // steps; 60 keys 725 -> 751)
+  const bool few = a.keys_cap <= 32;
+  if (a.D == 64 && few) hipLaunchKernelGGL((attn_f32_kernel<64, 64>), grid, dim3(64), 0, s, a);
+  else if (a.D == 64) hipLaunchKernelGGL((attn_f32_kernel<64, 256>), grid, dim3(256), 0, s, a);
+  else if (a.D == 128 && few) hipLaunchKernelGGL((attn_f32_kernel<128, 128>), grid, dim3(128), 0, s, a);
+  else if (a.D == 128) hipLaunchKernelGGL((attn_f32_kernel<128, 256>), grid, dim3(256), 0, s, a);
+  else if (a.D == 256) hipLaunchKernelGGL((attn_f32_kernel<256, 256>), grid, dim3(256), 0, s, a);
 }
 
 template <typename T>

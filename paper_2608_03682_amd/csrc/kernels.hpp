@@ -473,6 +473,7 @@ struct AttnArgs {
   const void* K; const void* Vt;
   int ldk;
   int keys_from_prefix, n_suffix;
+  int keys_cap;             // the most keys a query can have
   int mask_mode;
   void* out; int ldo;
   float* part;              // split partials (n_split > 1)

@@ -477,13 +477,16 @@ int attn_splits(int B, int M, int rows, int nkv, int keys, int D) {
   return best;
 }
 
-// key splits of block l's attention at batch B (DiT: even blocks attend to
-// the features, odd ones to the suffix)
+// The most keys a query of block l can have (DiT: even blocks attend to the
+// features, odd ones to the suffix).
+int attn_keys_cap(const phyai_expert& e, int l) {
+  return e.c.variant != PHYAI_VARIANT_DIT ? e.P + e.M : (l % 2 == 0 ? e.P : e.M);
+}
+
+// key splits of block l's attention at batch B
 int attn_split_of(const phyai_expert& e, int l, int B) {
   if (e.f32) return 1;
-  const int rows = e.M * (e.nq / e.nkv);
-  const int keys = e.c.variant != PHYAI_VARIANT_DIT ? e.P + e.M : (l % 2 == 0 ? e.P : e.M);
-  return attn_splits(B, e.M, rows, e.nkv, keys, e.D);
+  return attn_splits(B, e.M, e.M * (e.nq / e.nkv), e.nkv, attn_keys_cap(e, l), e.D);
 }
 
 // Whether block l's output projection merges the attention's key splits
@@ -595,6 +598,7 @@ void layer_stage(phyai_expert& e, int stage, int l, int k, int B, hipStream_t s)
   at.desc = e.desc;
   at.B = B; at.M = M; at.nq = e.nq; at.nkv = e.nkv; at.D = D;
   at.scale = inv_sqrt_d;
+  at.keys_cap = attn_keys_cap(e, l);
   at.n_split = attn_split_of(e, l, B);
   const bool merge_in_o = oproj_merges(e, l, B);
   at.defer_merge = merge_in_o ? 1 : 0;

@@ -22,6 +22,9 @@ torch = pytest.importorskip("torch")
     dict(head_dim=64, prefix_cap=8, prefix_min=0, prefix_max=0, horizon=5, batch=1),
     dict(head_dim=64, batch=1, horizon=2, state_token=False),
     dict(head_dim=64, batch=9, d_mlp=1024),
+    dict(head_dim=64, prefix_cap=12, prefix_min=0, prefix_max=12, horizon=19),        # 32 keys: D threads a block
+    dict(head_dim=128, n_q_heads=2, prefix_cap=12, prefix_min=3, prefix_max=12, horizon=19),
+    dict(head_dim=64, prefix_cap=13, prefix_min=13, prefix_max=13, horizon=19),       # 33: 256
 ])
 def test_fp32_path(kw):
     import paper_2608_03682_amd as px
