@@ -11,6 +11,7 @@
 
 #include <cstdlib>
 #include <cstring>
+#include <stdexcept>
 #include <type_traits>
 
 namespace phyai {
@@ -925,7 +926,6 @@ template <> struct WideEpi<EpiKV<float>> : std::false_type {};
 // ... and of these the ones it is built for with a second operand term
 template <class Epi> struct WideTwoTerm : std::false_type {};
 template <> struct WideTwoTerm<EpiResid> : std::true_type {};
-template <> struct WideTwoTerm<EpiGeglu<bf16_t>> : std::true_type {};
 template <> struct WideTwoTerm<EpiGegluLo> : std::true_type {};
 template <> struct WideTwoTerm<EpiQkv<bf16_t>> : std::true_type {};
 
@@ -950,28 +950,31 @@ void launch(const GemmArgs& g, const Epi& epi, hipStream_t s) {
       hipLaunchKernelGGL((gemm_f32_kernel<Epi, 4>), dim3(g.NPT, (g.R + 3) / 4), dim3(256), 0, s, g, epi);
     else
       hipLaunchKernelGGL((gemm_f32_kernel<Epi, 16>), dim3(g.NPT, (g.R + 15) / 16), dim3(256), 0, s, g, epi);
-  } else if (many && g.R >= 256 && g.A_lo == nullptr && g.A_ind == nullptr && g.rows_per_req == 0 && g.NPT % 4 == 0 &&
-             g.kind != W_FP4) {
-    const int tiles = gemm_tiles(g);
-    const char* force = getenv("PHYAI_GEMM_TILE");   // tests: "ring" / "deep" (read at enqueue time)
-    // widths that are no multiple of 256, and K splits (see above).  At most one
-    // tile per CU: no second block covers the load latency, so the four-stage
-    // ring with eight waves (two per SIMD); otherwise the two-stage ring
-    const int nz = g.split_out ? g.split_k : 1;       // K slices (gemm_split_k), deep ring only
-    const bool deep = !Epi::kWaveTile && (nz > 1 || (force ? strcmp(force, "deep") == 0 : tiles <= 256));
-    if (deep) {
-      const dim3 rgrid(xcd_grid(tiles), nz);
-      if constexpr (!Epi::kWaveTile) {
-        if (g.kind == W_FP8) hipLaunchKernelGGL((gemm_ring_kernel<Epi, true, 4, 4>), rgrid, dim3(512), 0, s, g, epi);
-        else hipLaunchKernelGGL((gemm_ring_kernel<Epi, false, 4, 4>), rgrid, dim3(512), 0, s, g, epi);
+  } else if (Terms<Epi>::kOne && many && g.R >= 256 && g.A_lo == nullptr && g.A_ind == nullptr &&
+             g.rows_per_req == 0 && g.NPT % 4 == 0 && g.kind != W_FP4) {
+    if constexpr (Terms<Epi>::kOne) {
+      const int tiles = gemm_tiles(g);
+      const char* force = getenv("PHYAI_GEMM_TILE");   // tests: "ring" / "deep" (read at enqueue time)
+      // widths that are no multiple of 256, and K splits (see above).  At most one
+      // tile per CU: no second block covers the load latency, so the four-stage
+      // ring with eight waves (two per SIMD); otherwise the two-stage ring
+      const int nz = g.split_out ? g.split_k : 1;       // K slices (gemm_split_k), deep ring only
+      const bool deep = !Epi::kWaveTile && (nz > 1 || (force ? strcmp(force, "deep") == 0 : tiles <= 256));
+      if (deep) {
+        const dim3 rgrid(xcd_grid(tiles), nz);
+        if constexpr (!Epi::kWaveTile) {
+          if (g.kind == W_FP8) hipLaunchKernelGGL((gemm_ring_kernel<Epi, true, 4, 4>), rgrid, dim3(512), 0, s, g, epi);
+          else hipLaunchKernelGGL((gemm_ring_kernel<Epi, false, 4, 4>), rgrid, dim3(512), 0, s, g, epi);
+        }
+      } else {
+        // eight waves per block too, except for the QKV epilogue, whose wave-tile
+        // form is written for 64 x 64 wave tiles
+        const dim3 rgrid(xcd_grid(tiles));
+        constexpr int WN = Epi::kWaveTile ? 2 : 4;
+        const dim3 blk(128 * WN);
+        if (g.kind == W_FP8) hipLaunchKernelGGL((gemm_ring_kernel<Epi, true, 2, WN>), rgrid, blk, 0, s, g, epi);
+        else hipLaunchKernelGGL((gemm_ring_kernel<Epi, false, 2, WN>), rgrid, blk, 0, s, g, epi);
       }
-    } else {
-      // eight waves per block too, except for the QKV epilogue, whose wave-tile
-      // form is written for 64 x 64 wave tiles
-      const dim3 rgrid(xcd_grid(tiles));
-      constexpr int WN = Epi::kWaveTile ? 2 : 4;
-      if (g.kind == W_FP8) hipLaunchKernelGGL((gemm_ring_kernel<Epi, true, 2, WN>), rgrid, dim3(128 * WN), 0, s, g, epi);
-      else hipLaunchKernelGGL((gemm_ring_kernel<Epi, false, 2, WN>), rgrid, dim3(128 * WN), 0, s, g, epi);
     }
   } else {
     // 32 columns and 16 * MT rows per block; K split over blockIdx.z only
@@ -983,8 +986,10 @@ void launch(const GemmArgs& g, const Epi& epi, hipStream_t s) {
       const dim3 grid(g.NPT, (g.R + 16 * MT - 1) / (16 * MT), nz);
       auto kind = [&](auto wk) {
         constexpr int WK = decltype(wk)::value;
-        if (two) hipLaunchKernelGGL((gemm_mfma_kernel<Epi, WK, true, 1, MT>), grid, dim3(256), 0, s, g, epi);
-        else hipLaunchKernelGGL((gemm_mfma_kernel<Epi, WK, false, 1, MT>), grid, dim3(256), 0, s, g, epi);
+        if constexpr (Terms<Epi>::kTwo)
+          if (two) hipLaunchKernelGGL((gemm_mfma_kernel<Epi, WK, true, 1, MT>), grid, dim3(256), 0, s, g, epi);
+        if constexpr (Terms<Epi>::kOne)
+          if (!two) hipLaunchKernelGGL((gemm_mfma_kernel<Epi, WK, false, 1, MT>), grid, dim3(256), 0, s, g, epi);
       };
       if (g.kind == W_FP8) kind(std::integral_constant<int, W_FP8>{});
       else if (g.kind == W_FP4) kind(std::integral_constant<int, W_FP4>{});
@@ -1003,6 +1008,7 @@ void gemm_store_bf16(const GemmArgs& g, const EpiStore<bf16_t>& e, hipStream_t s
 void gemm_store_f32(const GemmArgs& g, const EpiStore<float>& e, hipStream_t s) { launch(g, e, s); }
 void gemm_resid(const GemmArgs& g, const EpiResid& e, hipStream_t s) { launch(g, e, s); }
 void gemm_geglu_bf16(const GemmArgs& g, const EpiGeglu<bf16_t>& e, hipStream_t s) {
+  if ((e.lo == nullptr) != (g.A_lo == nullptr)) throw std::logic_error("GeGLU with a second term on one side only");
   if (e.lo) launch(g, EpiGegluLo{e}, s);
   else launch(g, e, s);
 }

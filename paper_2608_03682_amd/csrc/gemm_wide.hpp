@@ -137,7 +137,7 @@ __device__ __forceinline__ void wide_geglu(const GemmArgs& g, const EpiGeglu<bf1
       for (int i = 0; i < 4; ++i) {
         const float z = acc[m][2 * pp][i];
         v[pp][i] = (LO ? gelu_tanh_f(z) : gelu_tanh_bf16(z)) * acc[m][2 * pp + 1][i];
-        lo[pp][i] = v[pp][i] - ActIO<bf16_t>::round(v[pp][i]);
+        if constexpr (LO) lo[pp][i] = v[pp][i] - ActIO<bf16_t>::round(v[pp][i]);
       }
     const int64_t o = (int64_t)row * e.ldo + 16 * (p0 + lg % 2) + 8 * (lg / 2);
     *reinterpret_cast<uint4*>(e.out + o) = join_halves(v[0], v[1]);
@@ -147,8 +147,12 @@ __device__ __forceinline__ void wide_geglu(const GemmArgs& g, const EpiGeglu<bf1
 template <int MT>
 __device__ __forceinline__ void wide_epilogue(const GemmArgs& g, const EpiGeglu<bf16_t>& e, f32x4 (&acc)[MT][4],
                                               int row0, int p0, int lr, int lg, bf16_t*) {
-  if (e.lo) wide_geglu<true>(g, e, acc, row0, p0, lr, lg);
-  else wide_geglu<false>(g, e, acc, row0, p0, lr, lg);
+  wide_geglu<false>(g, e, acc, row0, p0, lr, lg);
+}
+template <int MT>
+__device__ __forceinline__ void wide_epilogue(const GemmArgs& g, const EpiGegluLo& e, f32x4 (&acc)[MT][4], int row0,
+                                              int p0, int lr, int lg, bf16_t*) {
+  wide_geglu<true>(g, e, acc, row0, p0, lr, lg);
 }
 
 // A wave's 64 columns lie in one head, so whether they are Q, K or V is known

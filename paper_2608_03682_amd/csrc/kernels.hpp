@@ -438,6 +438,13 @@ struct EpiKV {
   }
 };
 
+// Whether a GEMM with this epilogue may come without (kOne) and with (kTwo) a
+// second operand term: only such kernels are built.  The GeGLU has both terms or
+// neither on its way in and out.
+template <class Epi> struct Terms { static constexpr bool kOne = true, kTwo = true; };
+template <> struct Terms<EpiGeglu<bf16_t>> { static constexpr bool kOne = true, kTwo = false; };
+template <> struct Terms<EpiGegluLo> { static constexpr bool kOne = false, kTwo = true; };
+
 // The 256-column kernel's tile: 16 mt rows, ns stages (mt = 0: not taken).
 struct WideTile {
   int mt, ns;
@@ -446,6 +453,7 @@ void gemm_wide(const GemmArgs&, const EpiStore<bf16_t>&, WideTile, hipStream_t);
 void gemm_wide(const GemmArgs&, const EpiStore<float>&, WideTile, hipStream_t);
 void gemm_wide(const GemmArgs&, const EpiResid&, WideTile, hipStream_t);
 void gemm_wide(const GemmArgs&, const EpiGeglu<bf16_t>&, WideTile, hipStream_t);
+void gemm_wide(const GemmArgs&, const EpiGegluLo&, WideTile, hipStream_t);
 void gemm_wide(const GemmArgs&, const EpiQkv<bf16_t>&, WideTile, hipStream_t);
 void gemm_wide(const GemmArgs&, const EpiKV<bf16_t>&, WideTile, hipStream_t);
 
@@ -473,7 +481,6 @@ struct AttnArgs {
   const void* K; const void* Vt;
   int ldk;
   int keys_from_prefix, n_suffix;
-  int keys_cap;             // the most keys a query can have
   int mask_mode;
   void* out; int ldo;
   float* part;              // split partials (n_split > 1)
@@ -484,6 +491,7 @@ struct AttnArgs {
   const CallDesc* desc;
   int B, M, nq, nkv, D;
   float scale;              // 1/sqrt(D)
+  int keys_cap;             // the most keys a query can have
 };
 
 void attention_bf16(const AttnArgs&, hipStream_t);
@@ -557,7 +565,7 @@ struct EmbedArgs {
   const float* in_w;        // [A][d] fp32
   const float* in_b;        // [d]
   const float* rowvec;      // [d] also added to every action row, or null
-  int act;                  // Act applied to action rows
+  int act;                  // applied to action rows: ACT_NONE or ACT_SWISH
   const float* pos;         // [H][d] or null
   const float* e_state;     // [B][d] or null (state rows of h)
   float* h;                 // [B*M][d]: destination of state rows, and of action rows if act_out == null

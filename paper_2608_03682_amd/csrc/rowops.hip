@@ -297,6 +297,9 @@ __global__ __launch_bounds__(256) void norm_rows_wave_kernel(float* __restrict__
   }
 }
 
+// An embedding's activation: none or swish.
+__device__ __forceinline__ float embed_act(int act, float y) { return act == ACT_SWISH ? swish_f(y) : y; }
+
 // One block per suffix token row (b, t).
 __global__ __launch_bounds__(256) void embed_kernel(EmbedArgs e) {
   __shared__ float xs[64];
@@ -315,7 +318,7 @@ __global__ __launch_bounds__(256) void embed_kernel(EmbedArgs e) {
     for (int a = 0; a < e.A; ++a) y = fmaf(xs[a], e.in_w[(int64_t)a * e.d + c], y);
     if (e.rowvec) y += e.rowvec[c];
     if (e.pos) y += e.pos[(int64_t)j * e.d + c];
-    y = apply_act<float>(e.act, y);
+    y = embed_act(e.act, y);
     if (e.act_out) {
       const int64_t o = ((int64_t)b * e.H + j) * e.d + c;
       if (e.act_is_bf16) static_cast<bf16_t*>(e.act_out)[o] = f32_to_bf16(y);
@@ -399,7 +402,7 @@ __global__ __launch_bounds__(256) void embed_rows_kernel(EmbedArgs e) {
       for (int q = 0; q < 4; ++q) {
         if (e.rowvec) y[q] += r4[q];
         if (e.pos) y[q] += p4[q];
-        y[q] = apply_act<float>(e.act, y[q]);
+        y[q] = embed_act(e.act, y[q]);
       }
       const int j = t - e.off;
       if (e.act_out) {
@@ -773,7 +776,7 @@ __global__ __launch_bounds__(256) void readout_rows_kernel(ReadoutArgs r) {
       for (int q = 0; q < 4; ++q) {
         if (e.rowvec) y[q] += r4[q];
         if (e.pos) y[q] += p4[q];
-        y[q] = apply_act<float>(e.act, y[q]);
+        y[q] = embed_act(e.act, y[q]);
       }
       if (e.act_out) {
         const int64_t o = ((int64_t)b * e.H + j) * d + ec;
