@@ -58,15 +58,17 @@ _ATTN_SRC = ("paper_2608_03682_amd/csrc/attention.hip", "paper_2608_03682_amd/cs
 _GEMM_SRC = ("paper_2608_03682_amd/csrc/gemm.hip", "paper_2608_03682_amd/csrc/kernels.hpp",
              "paper_2608_03682_amd/csrc/common.hpp", "paper_2608_03682_amd/csrc/runtime.hip")
 _MERGE_SRC = _GEMM_SRC + ("paper_2608_03682_amd/csrc/attention.hip",)
+_WIDE_SRC = _GEMM_SRC + tuple("paper_2608_03682_amd/csrc/gemm_" + f for f in
+                             ("tile.hpp", "wide.hpp", "wide_geglu.hip", "wide_qkv.hip"))
 MEASURED_TRAFFIC = {
-    ("pi0_bf16_b1", "attn"): {"bytes": 6240129, "sources": _ATTN_SRC, "sha256": "fc85730cbaeea999"},
-    ("pi0_bf16_b1", "qkv"): {"bytes": 6536714, "sources": _GEMM_SRC, "sha256": "4fa368c185b08404"},
-    ("pi0_bf16_b1", "oproj"): {"bytes": 9340935, "sources": _MERGE_SRC, "sha256": "2a06dd1a5a827dc6"},
-    ("pi0_bf16_b1", "mlp_up"): {"bytes": 18212884, "sources": _GEMM_SRC, "sha256": "4fa368c185b08404"},
-    ("pi0_bf16_b1", "mlp_down"): {"bytes": 12464135, "sources": _GEMM_SRC, "sha256": "4fa368c185b08404"},
-    ("pi0_fp8_b64", "mlp_up"): {"bytes": 90550049, "sources": _GEMM_SRC, "sha256": "4fa368c185b08404"},
-    ("pi0_fp8_b64", "qkv"): {"bytes": 107004929, "sources": _GEMM_SRC, "sha256": "4fa368c185b08404"},
-    ("pi0_fp8_b64", "attn"): {"bytes": 84646916, "sources": _ATTN_SRC, "sha256": "fc85730cbaeea999"},
+    ("pi0_bf16_b1", "attn"): {"bytes": 6225792, "sources": _ATTN_SRC, "sha256": "e05bac8074f2bffb"},
+    ("pi0_bf16_b1", "qkv"): {"bytes": 6534666, "sources": _GEMM_SRC, "sha256": "7225f28a2d24692c"},
+    ("pi0_bf16_b1", "oproj"): {"bytes": 9340934, "sources": _MERGE_SRC, "sha256": "fc33e69c69a4e5e8"},
+    ("pi0_bf16_b1", "mlp_up"): {"bytes": 18204692, "sources": _GEMM_SRC, "sha256": "7225f28a2d24692c"},
+    ("pi0_bf16_b1", "mlp_down"): {"bytes": 12478471, "sources": _GEMM_SRC, "sha256": "7225f28a2d24692c"},
+    ("pi0_fp8_b64", "mlp_up"): {"bytes": 95415439, "sources": _WIDE_SRC, "sha256": "9d3498f9b8a75c26"},
+    ("pi0_fp8_b64", "qkv"): {"bytes": 57001359, "sources": _WIDE_SRC, "sha256": "9d3498f9b8a75c26"},
+    ("pi0_fp8_b64", "attn"): {"bytes": 84663309, "sources": _ATTN_SRC, "sha256": "e05bac8074f2bffb"},
 }
 
 

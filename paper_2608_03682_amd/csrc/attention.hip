@@ -572,10 +572,11 @@ __global__ __launch_bounds__(NT) void attn_f32_kernel(AttnArgs a) {
 // 0 .. prefix_len[b]-1.  Block: 64 keys x D of one (layer, request, head).
 // Moves are 16 bytes wide: K rows are copied directly; V rows go through an LDS
 // tile (rows padded by 16 bytes, which keeps them aligned and spreads a column
-// over the banks) and leave as runs of consecutive keys of one V^T row.  Bound by HBM: 64 requests x 18 layers
-// 560 us, 3.7 TB/s (933 us with the zero keys written one at a time), 8 x 18
-// 82 us (170), 1 x 18 14 us (17.5).  128- and 256-key tiles, 64- and 128-dim
-// blocks and loads four at a time all measured slower.
+// over the banks) and leave as runs of consecutive keys of one V^T row.  Bound
+// by HBM: 64 requests x 18 layers 560 us, 3.4 TB/s of measured traffic (933 us
+// with the zero keys written one at a time), 8 x 18 82 us (170), 1 x 18 14 us
+// (17.5).  128- and 256-key tiles, 64- and 128-dim blocks and loads four at a
+// time all measured slower.
 template <typename T, int D>
 __global__ __launch_bounds__(256) void prefix_relayout_kernel(RelayoutArgs r) {
   constexpr int VE = 16 / sizeof(T);           // elements per 16-byte move
@@ -691,9 +692,10 @@ __global__ __launch_bounds__(256) void kv_export_kernel(KvExportArgs r) {
 // blocks of all requests number fewer than 32 (below batch 8) and a request has
 // a suffix-sized query count, so that with the key splits the kernel spreads
 // over more CUs and each block loads half the queries and stores half the
-// partials (pi0 batch 1: 8.20 against 8.30 ms; batch 8: 15.9 against 15.6).  A prefix LM's self-attention (thousands of query rows per
-// request) keeps 128 rows: there four waves share each key tile (batch-1
-// prefix of 816 tokens: 63 -> 34 us per launch).  PHYAI_ATTN_ROWS=64|128
+// partials (pi0 batch 1: 8.20 against 8.30 ms; batch 8: 15.9 against 15.6).  A
+// prefix LM's self-attention (thousands of query rows per request) keeps 128
+// rows: there four waves share each key tile (batch-1 prefix of 816 tokens: 63
+// -> 34 us per launch).  PHYAI_ATTN_ROWS=64|128
 // (tests, read at enqueue time) forces it.
 int attention_rows_per_block(int B, int rows, int nkv) {
   const char* f = getenv("PHYAI_ATTN_ROWS");

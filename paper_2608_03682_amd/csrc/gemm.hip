@@ -935,9 +935,12 @@ void launch(const GemmArgs& g, const Epi& epi, hipStream_t s) {
   const bool many = g.row_ss == nullptr && g.fin_ctr == nullptr;
   if constexpr (WideEpi<Epi>::value) {
     const WideTile t = wide_tile(g);
-    // a K split without a second operand term keeps the 128 x 128 ring: its few
-    // tiles (768 x 4096 x 1024, 816 x 16384 x 2048) pay for the wide blocks' weight
-    // re-reads (tower 1.90 against 1.95 ms, prefix LM 0.87 against 0.95)
+    // A K split without a second operand term keeps the 128 x 128 ring.  With the
+    // wide tile instead, calls of two layers take: prefix LM of 816 rows (K =
+    // 16384, width 2048) + 7 %, pi0 width 2048 at 300 to 800 rows + 3 to 5 %,
+    // width 1024 in bf16 at 300 to 1,000 rows + 1 to 2 % (tower + 2 %), in fp8 at
+    // up to 500 rows - 1 to 2.5 %, widths 512 and 768 - 1.5 to 4 %, more rows within
+    // 1 %: the line follows the largest losses, not each width's best.
     if (many && t.mt > 0 && (g.A_lo ? WideTwoTerm<Epi>::value : !g.split_out)) {
       gemm_wide(g, epi, t, s);
       return;

@@ -13,11 +13,15 @@
 // Both operands of k-block kb + NS - 1 are requested while kb is computed.
 // NS = 2 keeps a wave within 256 registers, so that two blocks share a CU and
 // cover each other's waits; NS = 4 is for grids of at most one block per CU,
-// where weights come cold and nothing else hides their latency.  What then
-// bounds a step is the 32 KiB of weights per k-block entering the CU at about
-// 30 bytes a cycle: deeper rings (6, 8 stages), K halved over two wave groups,
-// loads spread between the MFMAs and a contiguous weight order all measured
-// the same or slower.
+// where weights come cold and nothing else hides their latency.  Counters: the
+// long grids keep the matrix cores 42 to 47 % busy (gate/up 816 x 2048 x 32768
+// bf16 1,194 TFLOP/s, 3264 x 1024 x 8192 fp8 1,132), LDS 11 to 12 % (the ring
+// 29 % at 720 TFLOP/s), the vector ALU 5 to 8 %, and take in 13 bytes of bf16
+// weights per CU and cycle; the one-block grids 11 to 26 %, 3 to 7 %, 2 to 4 %
+// and 10 to 16 bytes.  So no unit is saturated: what is left is the wait
+// for each k-block's loads, with one or two waves per SIMD to cover it.  Deeper
+// rings (6, 8 stages), K halved over two wave groups, loads spread between the
+// MFMAs and a contiguous weight order all measured the same or slower.
 //
 // The MFMAs run with the weights as the first operand: accumulator v of lane
 // l is column 16 t + 4 (l / 16) + v of row 16 m + l % 16, so a lane's four
