@@ -8,7 +8,7 @@ import pytest
 
 import oracle
 import workloads as wl
-from gpu_helpers import compare, run_gpu, small_cfg, to_device
+from gpu_helpers import compare, run_gpu, small_cfg, to_device, tolerance
 
 pytestmark = pytest.mark.gpu
 
@@ -35,6 +35,29 @@ def test_readout_four_rows(variant, kw):
     ex.close()
     ref = oracle.denoise(cfg, case.weights, case.prefix, case.prefix_len, case.noise, case.timesteps, case.state)
     compare(f"readout of four rows {variant} {kw}", gpu, ref, cfg)
+
+
+@pytest.mark.parametrize("kw", [dict(batch=65), dict(batch=65, d_model=1024, action_dim=14)])
+def test_readout_four_rows_dit(kw):
+    """The same with the DiT's LayerNorm, position rows and state token (1,040
+    rows), under weights that let the position rows decide: in the oracle,
+    dropping them moves the actions past the bar."""
+    import paper_2608_03682_amd as px
+    cfg = small_cfg("dit", n_layers=1, **kw)
+    print(f"[case] readout of four rows dit {kw}", flush=True)
+    pos = np.random.default_rng(21).standard_normal((cfg.horizon, cfg.d_model))
+    case = wl.make_case(cfg, seed=21, weights=wl.make_weights(cfg, 21, overrides={"pos_emb": pos}))
+    ex = px.Expert(cfg, case.weights)
+    gpu = run_gpu(ex, case)
+    ex.close()
+
+    def run(w):
+        return oracle.denoise(cfg, w, case.prefix, case.prefix_len, case.noise, case.timesteps, case.state)
+
+    ref = run(case.weights)
+    compare(f"readout of four rows dit {kw}", gpu, ref, cfg)
+    flat = wl.make_weights(cfg, 21, overrides={"pos_emb": 0 * pos})
+    assert np.abs(run(flat) - ref).max() > 2 * tolerance(cfg) * max(1.0, float(np.sqrt(np.mean(ref ** 2))))
 
 
 @pytest.mark.parametrize("variant,kw", [

@@ -12,7 +12,7 @@ import pytest
 
 import oracle
 import workloads as wl
-from gpu_helpers import compare, cross_case, run_gpu, small_cfg
+from gpu_helpers import compare, cross_case, run_gpu, small_cfg, tolerance
 
 pytestmark = pytest.mark.gpu
 
@@ -51,13 +51,17 @@ def test_wide_gemm_expert(tile, variant, kw):
 @pytest.mark.parametrize("tile", TILES, indirect=True)
 @pytest.mark.parametrize("wdt", ["bf16", "fp8"])
 def test_wide_gemm_keys_of_several_cross_blocks(tile, wdt):
-    """As test_dit_keys_of_several_cross_blocks, 450 feature rows."""
+    """As test_dit_keys_of_several_cross_blocks, 450 feature rows; rows a request
+    does not have leave zero keys whatever they hold."""
     import paper_2608_03682_amd as px
     cfg = small_cfg("dit", n_layers=4, weight_dtype=wdt, batch=5, prefix_cap=90, prefix_min=31, prefix_max=90)
     print(f"[case] wide tile {tile} dit, two cross blocks {wdt}", flush=True)
     case = cross_case(cfg, 17)
     ex = px.Expert(cfg, case.weights)
     gpu = run_gpu(ex, case)
+    assert case.prefix_len.min() < cfg.prefix_cap
+    case.prefix = wl.make_prefix(cfg, case.prefix_len, 17, pad_value=float("nan"))
+    assert np.array_equal(run_gpu(ex, case), gpu)
     ex.close()
     ref = oracle.denoise(cfg, case.weights, case.prefix, case.prefix_len, case.noise, case.timesteps, case.state)
     compare(f"wide tile {tile} dit, two cross blocks {wdt}", gpu, ref, cfg)
@@ -109,3 +113,32 @@ def test_wide_gemm_vision(tile, wdt):
     err = float(np.abs(got - ref).max())
     print(f"[parity] wide tile {tile} vision {wdt}: max_abs={err:.3e} bar={bar:.1e}", flush=True)
     assert np.isfinite(got).all() and err <= bar
+
+
+@pytest.mark.parametrize("variant", ["pi0", "pi05", "dit"])
+def test_schedule_tables_of_many_steps(variant):
+    """From 256 Euler steps on the timestep tables come from the many-row GEMMs
+    too.  300 steps, of which the last ten take all but 1e-3 of the way, and
+    timestep weights of 0.6: in the oracle, actions without them are off by ten
+    bars and more."""
+    import paper_2608_03682_amd as px
+    cfg = small_cfg(variant, n_layers=1, n_steps=300, horizon=5, batch=1)
+    print(f"[case] 300 steps {variant}", flush=True)
+    name = "time_w1" if variant == "pi0" else "cond_w1"
+    w = 0.02 * np.random.default_rng(20).standard_normal(wl.weight_specs(cfg)[name])
+    w[-cfg.time_dim:] *= 30
+    case = wl.make_case(cfg, seed=20, weights=wl.make_weights(cfg, 20, overrides={name: w}))
+    case.timesteps = np.concatenate([np.linspace(1, 0.999, 290, endpoint=False),
+                                     np.linspace(0.999, 0, 11)]).astype(np.float32)
+    ex = px.Expert(cfg, case.weights)
+    gpu = run_gpu(ex, case)
+    ex.close()
+
+    def run(weights):
+        return oracle.denoise(cfg, weights, case.prefix, case.prefix_len, case.noise, case.timesteps, case.state)
+
+    ref = run(case.weights)
+    compare(f"300 steps {variant}", gpu, ref, cfg)
+    w[-cfg.time_dim:] = 0
+    off = np.abs(run(wl.make_weights(cfg, 20, overrides={name: w})) - ref).max()
+    assert off > 10 * tolerance(cfg) * max(1.0, float(np.sqrt(np.mean(ref ** 2))))
